@@ -71,10 +71,39 @@ def couple_flops(N, nsteps, nh=4):
     return nsteps * (48 * M * (2 * M + 1) + 2 * M)
 
 
-def stepper_flops(tsk, op, N, nsteps):
-    """Flop model and kernel name of the stepper the operator's matvec runs."""
+def power_tiles(N, nh=4):
+    return ((2 * ((N - 1) // 3) + 1 + nh - 1) // nh + 15) // 16
+
+
+def integrates_by_squaring(N, nsteps, fp32, nh=4):
+    """Whether a plain matvec of a one-harmonic base flow squares the step matrix of
+    its chains (the library's rule: step counts by tiles of 16 modes)."""
+    t = power_tiles(N, nh)
+    least = ((16, 24, 56, None, 80, 80) if fp32 else (16, 28, 72, 176, 120, 120))
+    return t <= 6 and 1 + (N - 1) // 3 * (nh // 2 + 1) <= 768 and least[t - 1] is not None and nsteps >= least[t - 1]
+
+
+def power_flops(N, nsteps, nh=4):
+    """Flops of one matvec by squaring as executed: per chain pair the squarings on
+    16 x 16 tiles (those of chains of four and more tiles on the band while it is
+    at most 16 wide) and the matrix-vector products on four columns."""
+    t = power_tiles(N, nh)
+    ratio = 1 if t <= 2 else 3 if t == 3 else 5 if t == 4 else 7
+    k = 0
+    while (nsteps >> k) - (nsteps >> (k + 1)) > ratio:
+        k += 1
+    tiles = sum(9 * t if t >= 4 and 4 << q <= 16 else t ** 3 for q in range(k))
+    products = bin(nsteps & ((1 << k) - 1)).count("1") + (nsteps >> k)
+    return (N - 1) // 3 * (nh // 2 + 1) * (tiles * 2 * 16 ** 3 + products * 2 * 4 * (16 * t) ** 2)
+
+
+def stepper_flops(tsk, op, N, nsteps, stepped=False):
+    """Flop model and kernel name of the stepper the operator's matvec runs (stepped:
+    in a singular-value run, which never squares)."""
     t = tsk.get_tuning(op)
     rt = "double" if op.elem_bytes == 8 else "float"
+    if t == -2 and not stepped and integrates_by_squaring(N, nsteps, op.elem_bytes == 4):
+        return power_flops(N, nsteps), f"k_couple_power<{rt},{power_tiles(N)}>"
     if t == -2:
         M = (N - 1) // 3
         return couple_flops(N, nsteps), f"k_colstep_couple<{rt},{1 if (2 * M + 1 + 3) // 4 <= 64 else 2}>"
@@ -226,7 +255,9 @@ def run_single(args, tsk, W, np, torch, cfg, prec, dtype_name):
     flops, kernel = stepper_flops(tsk, op, N, nsteps)
     traffic = None
     wkey = f"traffic_bytes_per_launch_w{tsk.get_stepper_waves(op)}"  # the launch shape the library kept
-    if stepper == -2 and prec == tsk.TSK_FP64 and N == 128:
+    if "power" in kernel:
+        pass  # no counters taken for the squaring kernel
+    elif stepper == -2 and prec == tsk.TSK_FP64 and N == 128:
         traffic = measured_traffic("k_colstep_couple_kolmo128_fp64_hbm_traffic.md", key=wkey)
     elif stepper == -2 and prec == tsk.TSK_FP32 and N == 256:
         traffic = measured_traffic("k_colstep_couple_kolmo256_fp32_hbm_traffic.md", key=wkey)
@@ -369,7 +400,7 @@ def run_optimal(args, tsk, W, np, torch):
     # forward integrations by the operator's stepper, adjoint ones by its transpose: the transposed
     # coupling stepper does the same arithmetic per chain as the forward one; the transposed column
     # stepper (other stepper choices) has the column stepper's flops.  Flops averaged over the two kinds
-    fwd_flops, fwd_kernel = stepper_flops(tsk, op, N, nsteps)
+    fwd_flops, fwd_kernel = stepper_flops(tsk, op, N, nsteps, stepped=True)
     coupled = tsk.get_tuning(op) == -2
     adj_flops = fwd_flops if coupled else colstep_flops(N, nsteps)
     adj_kernel = (fwd_kernel.replace("k_colstep_couple", "k_colstep_couple_adj") if coupled
@@ -746,8 +777,9 @@ def run_learned(args, tsk, W, np, torch):
     launch_ms = stats["fp32_learned"]["ms_per_matvec"]
     flops, kname = stepper_flops(tsk, o32[0], N, nsteps)
     achieved = flops / (launch_ms / 1e3) / 1e12
-    traffic = measured_traffic("k_colstep_couple_kolmo256_fp32_hbm_traffic.md",
-                               key=f"traffic_bytes_per_launch_w{tsk.get_stepper_waves(o32[0])}")
+    traffic = None if "power" in kname else measured_traffic(
+        "k_colstep_couple_kolmo256_fp32_hbm_traffic.md",
+        key=f"traffic_bytes_per_launch_w{tsk.get_stepper_waves(o32[0])}")
     sweep_stats = run_sweep_tsgp(tsk, W, torch)
     for name in forms:
         stats[name]["tsgp_per_s"] = stats[name]["mean_matvecs"] * nsteps * N * N / (stats[name]["ms_per_solve"] / 1e3)

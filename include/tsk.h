@@ -8,7 +8,9 @@
  *     exponential propagator M = exp(A T) (Sec. 2.2; Sec. 3.2, eq. "discrete-time
  *     linear system"); lambda = log(mu) / T.
  *   - M is never formed: one matvec M x is one time integration of the
- *     linearized equations over T (Sec. 3, "time-stepper" approach).
+ *     linearized equations over T (Sec. 3, "time-stepper" approach).  Where the
+ *     modes split into short uncoupled chains, the identical steps of a chain may
+ *     be taken by repeated squaring of its one-step matrix instead of one by one.
  *   - Ritz pairs come from the m-step Arnoldi factorisation (Sec. 3.2.1,
  *     eq. "m-step Arnoldi", Algorithm 1) and are accepted by the residual
  *     |beta e_m^T y| (Sec. 3.2.2, eq. "Krylov convergence").
@@ -123,10 +125,11 @@ tsk_status tsk_set_base_flow(tsk_op op, const double* U, const double* V,
  * choose: for a base profile of one harmonic, U = amp sin(n (y - y0)) with
  * dOmega/dy = c U (the Kolmogorov flow sin 4y), the spectral-coupling stepper:
  * the product with one harmonic couples ky only to ky +- n, so each kx column
- * splits into n chains advanced by one wavefront each with a three-point
- * coupling and no transforms; with the 2/3 rule nothing of the pseudo-spectral
- * product wraps onto a kept mode (n < N - 2M), so it is the same operator to
- * rounding.  Otherwise the column stepper, whose kx columns per 64-lane
+ * splits into n chains with a three-point coupling and no transforms; with the
+ * 2/3 rule nothing of the pseudo-spectral product wraps onto a kept mode
+ * (n < N - 2M), so it is the same operator to rounding.  A chain is advanced
+ * step by step by one wavefront or, where that is faster, by repeated squaring of
+ * its one-step matrix within the call (nothing is kept between calls).  Otherwise the column stepper, whose kx columns per 64-lane
  * wavefront (1 or 2, 2 only for N <= 256) the library times on the first matvec
  * of a given size, precision, base kind and launch size and keeps for the
  * process.  1 or 2 force that column variant (both compute every column with
@@ -140,8 +143,9 @@ tsk_status tsk_set_base_flow(tsk_op op, const double* U, const double* V,
 tsk_status tsk_set_tuning(tsk_op op, int columns_per_wave);
 tsk_status tsk_get_tuning(tsk_op op, int* columns_per_wave);
 
-/* Launch shape of the spectral-coupling stepper: 64-lane wavefronts per
- * workgroup (1, 2 or 4; one chain per wavefront in every shape, so the results
+/* Launch shape of the spectral-coupling stepper (of chains advanced step by step;
+ * integrations by squaring have a shape of their own and report 4): 64-lane
+ * wavefronts per workgroup (1, 2 or 4; one chain per wavefront in every shape, so the results
  * are the same bits).  0 (the default) lets the library time the three shapes
  * on the first launch of a given precision, chain layout and launch size (a
  * single matvec, or a batch's shared launch) and keep the fastest for the

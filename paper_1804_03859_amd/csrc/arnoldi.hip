@@ -335,8 +335,7 @@ tsk_status arnoldi_t(Operator* const* ops, int count, int m, int k, double tol, 
             if (oc[i].done) continue;
             const TS* vj = static_cast<TS*>(Dh[i].V) + j * Dh[i].ldv;
             if (svd) {  // M^dagger M v_j: forward, then adjoint integration
-                TSK_TRY(ops[i]->apply(vj, ops[i]->aw.tmp.ptr));
-                TSK_TRY(ops[i]->apply_adjoint(ops[i]->aw.tmp.ptr, Dh[i].w));
+                TSK_TRY(ops[i]->normal_product(vj, ops[i]->aw.tmp.ptr, Dh[i].w));
             } else {
                 TSK_TRY(ops[i]->apply(vj, Dh[i].w));
             }

@@ -38,6 +38,7 @@
 #include "colbloch.hpp"
 #include "colcouple.hpp"
 #include "colcouple_adj.hpp"
+#include "colpower.hpp"
 #include "colstep.hpp"
 #include "kolmo2d.hpp"
 #include "krylov.hpp"
@@ -406,6 +407,51 @@ void launch_couple_adj(const ColInst<real>& one, int blocks, int S, int wpw, hip
         launch_couple_adj_shape<real, 2>(one, blocks, wpw, s);
 }
 
+// Repeated-squaring integration (colpower.hpp) of one instance.
+template <typename F> tsk_status power_lds(F* kernel, int lds) {
+    if (lds > 64 * 1024)
+        TSK_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    return TSK_OK;
+}
+template <typename real, bool ADJ, int TC>
+tsk_status launch_power_tiles(const ColInst<real>& one, hipStream_t s) {
+    constexpr int lds = power_lds_bytes<real, TC>();
+    static_assert(lds <= 160 * 1024, "LDS of one compute unit");
+    TSK_TRY(power_lds(&k_couple_power<real, TC, ADJ>, lds));
+    hipLaunchKernelGGL((k_couple_power<real, TC, ADJ>), dim3(power_blocks(one.M, one.nh)),
+                       dim3(power_waves(TC) * kWave), lds, s, one);
+    TSK_HIP(hipGetLastError());
+    return TSK_OK;
+}
+template <typename real, bool ADJ> tsk_status launch_power(const ColInst<real>& one, hipStream_t s) {
+    switch (power_tiles(one.M, one.nh)) {
+        case 1: return launch_power_tiles<real, ADJ, 1>(one, s);
+        case 2: return launch_power_tiles<real, ADJ, 2>(one, s);
+        case 3: return launch_power_tiles<real, ADJ, 3>(one, s);
+        case 4: return launch_power_tiles<real, ADJ, 4>(one, s);
+        case 5: return launch_power_tiles<real, ADJ, 5>(one, s);
+        case 6: return launch_power_tiles<real, ADJ, 6>(one, s);
+        default: return fail(TSK_EINVAL, "chain too long for the squaring integration");
+    }
+}
+
+// ... and of n instances of a batch (grid y), the longest chain in `tiles` tiles.
+template <typename real>
+tsk_status launch_power_batch(const ColInst<real>* insts, const int* ids, int n, int jstep, int blocks, int tiles,
+                              hipStream_t s) {
+    constexpr int lds[kPowMaxTiles] = {power_lds_bytes<real, 1>(), power_lds_bytes<real, 2>(),
+                                       power_lds_bytes<real, 3>(), power_lds_bytes<real, 4>(),
+                                       power_lds_bytes<real, 5>(), power_lds_bytes<real, 6>()};
+    int waves = 1;
+    for (int t = 1; t <= tiles; ++t) waves = std::max(waves, power_waves(t));
+    TSK_TRY(power_lds(&k_couple_power_batch<real>, lds[tiles - 1]));
+    hipLaunchKernelGGL((k_couple_power_batch<real>), dim3(blocks, n), dim3(waves * kWave), lds[tiles - 1], s, insts,
+                       ids, jstep);
+    TSK_HIP(hipGetLastError());
+    return TSK_OK;
+}
+
 // Launch shape of the coupling stepper (wavefronts per workgroup: 1, 2 or 4),
 // timed once per (precision, positions per lane, launch size) and process on
 // the first real launch, like the column variants; the shapes compute the same
@@ -483,6 +529,27 @@ tsk_status couple_choice(const CoupleKey& key, hipStream_t s, F&& launch, int* o
 // Positions per lane of the coupling stepper for cutoff M and harmonic nh: the
 // longest chain has ceil((2M + 1) / nh) modes.
 inline int couple_slots(int M, int nh) { return ((2 * M + 1 + nh - 1) / nh + kWave - 1) / kWave; }
+
+// Squaring (colpower.hpp) or stepping: the smallest step count at which a single
+// matvec by squaring is the faster one, by the tiles of the longest chain.
+// Stepping / squaring in us, FP64 (FP32), 4 chains per column: 96^2 (1 tile) 16
+// steps 5.1 / 5.1 (4.6 / 4.7), 32 steps 7.3 / 5.4 (6.2 / 4.9); 128^2 (2) 16 steps
+// 5.1 / 6.1, 32 steps 7.3 / 6.7, 200 steps 30.3 / 9.0 (23.5 / 7.2); 256^2 (3) 64 steps
+// 11.9 / 12.1 (9.6 / 9.1), 200 steps 30.4 / 15.4 (23.6 / 11.4); 384^2 (4) 100 steps
+// 17.7 / 23.6, 200 steps 31.4 / 28.4; 512^2 (6) 100 steps 45.0 / 47.4 (29.0 / 25.1), 200
+// steps 84.8 / 64.9 (52.9 / 34.5).  FP32 chains of 4 tiles step: 384^2 alone would
+// gain (24.0 / 19.3), but a batch fills the device with them and is bound by the
+// matrix cores (the 64-instance sweep's lockstep matvec 286 / 333 us).  Launches of
+// more than 768 workgroups (profiles of 6 and more periods on the largest grids)
+// queue for compute units and step.  The rule looks at the operator alone, so a
+// batch gives the bits of single runs.
+inline bool power_pays(int M, int nh, int nsteps, bool fp32) {
+    constexpr int kMin64[kPowMaxTiles] = {16, 28, 72, 176, 120, 120};
+    constexpr int kNever = 1 << 30;
+    constexpr int kMin32[kPowMaxTiles] = {16, 24, 56, kNever, 80, 80};
+    const int tiles = power_tiles(M, nh);
+    return tiles <= kPowMaxTiles && power_blocks(M, nh) <= 768 && nsteps >= (fp32 ? kMin32 : kMin64)[tiles - 1];
+}
 
 struct KolmoOp final : Operator {
     int N = 0, M = 0;
@@ -579,14 +646,34 @@ struct KolmoOp final : Operator {
     bool use_couple() const { return !gen && couple && force_cols == 0; }
     bool use_bloch() const { return !gen && bloch && (force_cols == 3 || (force_cols == 0 && !couple)); }
 
+    bool use_power() const { return use_couple() && power_pays(M, nh, nsteps, prec == TSK_FP32); }
+
     template <typename real> void launch_bloch(const void* x, void* y) const {
         launch_bloch_stepper<real>(N, inst<real>(x, 0, y, nullptr), nullptr, nullptr, 1, 0, tw.as<cplx<real>>(),
                                    stream);
     }
-    tsk_status apply(const void* x, void* y) override {
+    tsk_status apply(const void* x, void* y) override { return forward(x, y, use_power()); }
+    // M^T M x of the singular-value runs, always step by step.  The x-translation
+    // symmetry of a parallel base makes singular values double, and the second
+    // copies, which these runs return, enter the Krylov space only through the
+    // rounding of the integration: some 800 rounded stages per matvec.  Squaring
+    // applies the same matrix to the real and imaginary parts and rounds a few
+    // products, so the copies would come several steps too late to be returned.
+    tsk_status normal_product(const void* x, void* mid, void* y) override {
+        TSK_TRY(forward(x, mid, false));
+        return backward(mid, y, false);
+    }
+    // square: by repeated squaring (colpower.hpp), where use_power() allows it
+    tsk_status forward(const void* x, void* y, bool square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply: input and output must not alias");
         if (gen) return gen2d_apply(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
+        if (square) {
+            tuned_wpw = 4;
+            if (prec == TSK_FP32)
+                return launch_power<float, false>(inst<float>(x, 0, y, nullptr), stream);
+            return launch_power<double, false>(inst<double>(x, 0, y, nullptr), stream);
+        }
         if (use_couple()) {
             const int S = couple_slots(M, nh), blocks = couple_blocks(M, nh);
             auto launch = [&](int w) {
@@ -637,10 +724,16 @@ struct KolmoOp final : Operator {
     // kept, else one wavefront per workgroup); other parallel bases the
     // transposed column stepper (k_colstep_adj, task list of 1-column tasks);
     // a general 2-D base the transposed pipeline of kolmo2d.hip.
-    tsk_status apply_adjoint(const void* x, void* y) override {
+    tsk_status apply_adjoint(const void* x, void* y) override { return backward(x, y, use_power()); }
+    tsk_status backward(const void* x, void* y, bool square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply_adjoint: input and output must not alias");
         if (gen) return gen2d_apply_adjoint(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
+        if (square) {
+            if (prec == TSK_FP32)
+                return launch_power<float, true>(inst<float>(x, 0, y, nullptr), stream);
+            return launch_power<double, true>(inst<double>(x, 0, y, nullptr), stream);
+        }
         if (use_couple()) {
             const int S = couple_slots(M, nh), blocks = couple_blocks(M, nh);
             const int w = force_wpw ? force_wpw : (tuned_wpw ? tuned_wpw : 1);
@@ -1005,6 +1098,9 @@ struct KolmoBatch {
         int cwpw = 1;                 // its launch shape (wavefronts per workgroup, tuned)
         DevBuf ids;  // Bloch and coupling groups: instance indices
         int nids = 0;
+        // coupling group: its instances that integrate by squaring (ids: the others)
+        DevBuf pids;
+        int npids = 0, pblocks = 0, ptiles = 0;
         const void* tw;
         DevBuf tasks[3];  // task lists for 1 and 2 columns per wavefront
         int ntasks[3] = {0, 0, 0};
@@ -1052,6 +1148,7 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
     TSK_HIP(hipMemcpy(b->insts.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
     b->host_insts = host;
     std::vector<std::vector<int>> gids;
+    std::vector<int> pids;  // of the coupling group (there is one at most)
     for (int i = 0; i < count; ++i) {
         const bool kc = kolmo_couple(ko[i]);
         const bool kb = !kc && kolmo_bloch(ko[i]);
@@ -1061,12 +1158,13 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
             if ((kc && c->couple) ||
                 (!kc && !c->couple && c->N == ko[i]->N && c->prop == ko[i]->prop && c->bloch == kb)) {
                 g = c;
-                gids[q].push_back(i);
+                if (!(kc && ko[i]->use_power())) gids[q].push_back(i);
             }
         }
         if (!g) {
             b->groups.push_back(std::make_unique<KolmoBatch::Group>());
-            gids.push_back({i});
+            gids.push_back({});
+            if (!(kc && ko[i]->use_power())) gids.back().push_back(i);
             g = b->groups.back().get();
             g->N = ko[i]->N;
             g->prop = ko[i]->prop;
@@ -1076,7 +1174,11 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
             g->force = ko[i]->force_cols;
         }
         g->columns += ko[i]->M + 1;
-        if (kc) {
+        if (kc && ko[i]->use_power()) {
+            pids.push_back(i);
+            g->pblocks = std::max(g->pblocks, power_blocks(ko[i]->M, ko[i]->nh));
+            g->ptiles = std::max(g->ptiles, power_tiles(ko[i]->M, ko[i]->nh));
+        } else if (kc) {
             g->cblocks = std::max(g->cblocks, couple_blocks(ko[i]->M, ko[i]->nh));
             g->cslots = std::max(g->cslots, couple_slots(ko[i]->M, ko[i]->nh));
             if (ko[i]->force_wpw) g->cwpw = ko[i]->force_wpw;
@@ -1086,7 +1188,13 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
     for (size_t q = 0; q < b->groups.size(); ++q) {
         KolmoBatch::Group* g = b->groups[q].get();
         if (!g->bloch && !g->couple) continue;
+        if (g->couple && !pids.empty()) {
+            g->npids = int(pids.size());
+            TSK_TRY(g->pids.ensure(pids.size() * sizeof(int)));
+            TSK_HIP(hipMemcpy(g->pids.ptr, pids.data(), pids.size() * sizeof(int), hipMemcpyHostToDevice));
+        }
         g->nids = int(gids[q].size());
+        if (g->nids == 0) continue;
         TSK_TRY(g->ids.ensure(gids[q].size() * sizeof(int)));
         TSK_HIP(hipMemcpy(g->ids.ptr, gids[q].data(), gids[q].size() * sizeof(int), hipMemcpyHostToDevice));
     }
@@ -1110,7 +1218,7 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
         if (g->couple) {
             // the launch shape: forced by an instance of the group, else timed on the
             // step-0 inputs (the outputs are overwritten by the first real matvec)
-            if (g->force) continue;
+            if (g->force || g->nids == 0) continue;
             KolmoBatch::Group* gp = g.get();
             KolmoBatch* bp = b.get();
             auto launch = [&](int w) {
@@ -1165,11 +1273,19 @@ tsk_status kolmo_batch_matvec(KolmoBatch* b, int j, hipStream_t s) {
         hipStream_t st = q == 0 ? s : b->aux[q - 1];
         if (q > 0) TSK_HIP(hipStreamWaitEvent(st, b->fork, 0));
         const int c = g->cols;
-        if (g->couple) {
+        if (g->npids > 0) {
             if (b->fp32)
+                TSK_TRY(launch_power_batch<float>(b->insts.as<ColInst<float>>(), g->pids.as<int>(), g->npids, j,
+                                                  g->pblocks, g->ptiles, st));
+            else
+                TSK_TRY(launch_power_batch<double>(b->insts.as<ColInst<double>>(), g->pids.as<int>(), g->npids, j,
+                                                   g->pblocks, g->ptiles, st));
+        }
+        if (g->couple) {
+            if (g->nids > 0 && b->fp32)
                 launch_couple_stepper<float>(ColInst<float>{}, b->insts.as<ColInst<float>>(), g->ids.as<int>(),
                                              g->nids, j, g->cblocks, g->cslots, g->cwpw, st);
-            else
+            else if (g->nids > 0)
                 launch_couple_stepper<double>(ColInst<double>{}, b->insts.as<ColInst<double>>(), g->ids.as<int>(),
                                               g->nids, j, g->cblocks, g->cslots, g->cwpw, st);
         } else if (g->bloch) {

@@ -123,6 +123,11 @@ struct Operator {
         return fail(TSK_EINVAL, std::string("no adjoint propagator for ") + name());
     }
     virtual bool has_adjoint() const { return false; }
+    // y = M^dagger M x with mid = M x (a Lanczos step of the singular-value runs)
+    virtual tsk_status normal_product(const void* x, void* mid, void* y) {
+        TSK_TRY(apply(x, mid));
+        return apply_adjoint(mid, y);
+    }
     virtual tsk_status from_physical(const void* phys, void* state) = 0;
     virtual tsk_status to_physical(const void* state, void* phys) = 0;
     // Number of reals in the physical field (complex fields count 2 per value).
