@@ -9,7 +9,7 @@
  *     linear system"); lambda = log(mu) / T.
  *   - M is never formed: one matvec M x is one time integration of the
  *     linearized equations over T (Sec. 3, "time-stepper" approach).  Where the
- *     modes split into short uncoupled chains, the identical steps of a chain may
+ *     modes split into uncoupled chains or columns, the identical steps of one may
  *     be taken by repeated squaring of its one-step matrix instead of one by one.
  *   - Ritz pairs come from the m-step Arnoldi factorisation (Sec. 3.2.1,
  *     eq. "m-step Arnoldi", Algorithm 1) and are accepted by the residual
@@ -129,10 +129,14 @@ tsk_status tsk_set_base_flow(tsk_op op, const double* U, const double* V,
  * 2/3 rule nothing of the pseudo-spectral product wraps onto a kept mode
  * (n < N - 2M), so it is the same operator to rounding.  A chain is advanced
  * step by step by one wavefront or, where that is faster, by repeated squaring of
- * its one-step matrix within the call (nothing is kept between calls).  Otherwise the column stepper, whose kx columns per 64-lane
- * wavefront (1 or 2, 2 only for N <= 256) the library times on the first matvec
- * of a given size, precision, base kind and launch size and keeps for the
- * process.  1 or 2 force that column variant (both compute every column with
+ * its one-step matrix within the call (nothing is kept between calls).  Other
+ * profiles: tsk_apply and tsk_apply_adjoint of many steps square the one-step
+ * matrices of whole columns where that is faster (a workspace of four matrices per
+ * column is allocated on first use; captured calls and calls that find no memory
+ * step); otherwise, and in the Arnoldi drivers, the column stepper, whose kx
+ * columns per 64-lane wavefront (1 or 2, 2 only for N <= 256) the library times on
+ * the first matvec of a given size, precision, base kind and launch size that steps
+ * and keeps for the process.  1 or 2 force that column variant (both compute every column with
  * the same arithmetic, so results do not depend on the choice); 3 forces the
  * Bloch-sector stepper where it applies (N = 128, 256 or 512 and a profile of
  * period 2 pi / 4 with a single harmonic: each column split into the four

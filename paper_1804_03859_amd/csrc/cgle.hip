@@ -327,13 +327,11 @@ __global__ __launch_bounds__(kCgleMaxN) void k_cgle_form(CnJob one, const CnJob*
     }
 }
 
-// Stepping or squaring, from measured costs in us (8 XCDs, one integration): a step
-// one exchange after the other (256 nodes, 4 levels 0.39, 400 nodes 0.51, 1000 nodes, 6
-// levels 1.28); forming the matrix 8; a doubling the launch and the loads' latency, or
-// the matrix cores' time (n = 24 4, 128 9, 256 17, 400 24, 1000 118); an application one
-// launch.  100 steps at 256 nodes: 41 stepping, 106 squaring; 23000 steps at 400 nodes:
-// 13100 and 349.  The rule looks at one integration alone, so a batch gives the bits
-// of single runs.
+// Stepping or squaring, from estimated times in us: a step is one exchange after the
+// other (256 nodes, 4 levels 0.39, 400 nodes 0.51, 1000 nodes, 6 levels 1.28), forming the
+// matrix 8, doublings and applications as in cpower.hpp.  100 steps at 256 nodes: 41
+// stepping, 106 squaring; 23000 steps at 400 nodes: 13100 and 340.  The rule looks at one
+// integration alone, so a batch gives the bits of single runs.
 struct CnPlan {
     bool square = false;
     int doublings = 0;
@@ -341,10 +339,11 @@ struct CnPlan {
 inline CnPlan cn_plan(const CnJob& jb) {
     const double n = jb.n;
     const double step = jb.n <= 512 ? ((jb.levels + 1) / 2) * (0.13 + 0.0003 * n) : 0.2 * jb.levels;
-    const double dbl = std::max(4.0 + 0.05 * n, 8.0 * n * n * n / 6.6e7), app = 3.3 + 0.001 * n;
+    const CpowCost c{CpowWork::ld_of(jb.n, 1), 1, CpowWork::tiles_of(jb.n, 1), false};
+    double cost = 0.0;
     CnPlan p;
-    p.doublings = cpow_doublings(jb.nsteps, dbl / app);
-    p.square = 8.0 + p.doublings * dbl + double(jb.nsteps >> p.doublings) * app < 0.8 * step * jb.nsteps;
+    p.doublings = c.doublings(jb.nsteps, c.ld, &cost);
+    p.square = 8.0 + cost < 0.8 * step * jb.nsteps;
     return p;
 }
 
@@ -369,7 +368,7 @@ tsk_status cn_square(const CpowWork& W, const CnPlan& p, const CnJob& one, const
     else
         hipLaunchKernelGGL(k_cgle_form<2>, dim3((W.ld + 1) / 2 + 1, count), dim3(nt), 2 * 2 * nt * sizeof(double2), s,
                            one, jobs, j, f);
-    return cpow_run<double>(W, one.nsteps, forced, p.doublings, out, s);
+    return cpow_run<double>(W, one.nsteps, forced, W.ld, p.doublings, out, s);
 }
 
 struct CgleOp final : Operator {
@@ -525,19 +524,11 @@ struct CgleOp final : Operator {
         jb.in = static_cast<const double2*>(x);
         jb.out = static_cast<double2*>(y);
         const CnPlan p = cn_plan(jb);
-        if (p.square && workspace_ready()) {
+        if (p.square && pow.ready(nn, 1, sizeof(double), stream)) {
             CpowOut<double> out{reinterpret_cast<double*>(y), 0, nullptr, nn};
             return cn_square(pow, p, jb, nullptr, 1, 0, threads(), resolvent, out, stream);
         }
         return launch_cn_levels(jb.levels, jb, nullptr, 1, 0, threads(), stream);
-    }
-    // The squaring workspace; without it (no memory, or a capturing stream, which
-    // cannot allocate) the integration steps.
-    bool workspace_ready() {
-        if (pow.fits(nn, 1, sizeof(double))) return true;
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-        return pow.ensure(nn, 1, sizeof(double)) == TSK_OK;
     }
     tsk_status apply(const void* x, void* y) override { return run(false, x, y); }
     // M^H: Crank-Nicolson with L_h^H (the two factors of a step commute, so this is
@@ -704,11 +695,11 @@ tsk_status cgle_batch_plan(Operator* const* ops, int count, const KryDesc* D_hos
     p->threads = c0->threads();
     p->two = svd;
     // matrices squared at once: at most 1 GiB of them
-    const size_t each = CpowWork::bytes((c0->nn + 31) / 32 * 32, sizeof(double));
+    const size_t each = 2 * CpowWork::bytes((c0->nn + 31) / 32 * 32, sizeof(double));
     p->chunk = int(std::min<size_t>(size_t(count), std::max<size_t>(1, (size_t(1) << 30) / each)));
     bool any = false;
     for (int i = 0; i < count; ++i) any = any || cn_plan(a[i]).square;
-    if (any && c0->pow.ensure(c0->nn, p->chunk, sizeof(double)) == TSK_OK) p->work = &c0->pow;
+    if (any && c0->pow.ready(c0->nn, p->chunk, sizeof(double), c0->stream)) p->work = &c0->pow;
     TSK_TRY(cgle_pass_plan(p.get(), a, &p->first));
     if (svd) TSK_TRY(cgle_pass_plan(p.get(), b, &p->second));
     *out = std::move(p);

@@ -14,16 +14,26 @@
 // doublings alternate between.  Vectors: four planes (v re, v im, q re, q im) per
 // matrix, two buffers.
 //
+// Bands: a matrix whose entries vanish beyond a distance from the diagonal is stored
+// with only its blocks |bi - bj| <= band valid (blocks of 16 MT, what one wavefront
+// computes; ld / (16 MT) or more: all), and a doubling doubles the band; blocks
+// outside are neither written nor read.
+//
 // k_cpow_gemm: one wavefront per MT x MT tiles of 16 x 16, four products
 // v_mfma_{f64,f32}_16x16x4 per complex tile product; the fragments come straight
 // from global memory (a lane's four A values are consecutive, the k index of MFMA r
-// is 16 g + 4 (lane / 16) + r), the next 16 k loaded while the current ones
+// is 16 g + 4 (lane / 16) + r), the next 16 or 48 k loaded while the current ones
 // multiply.  The matrices of a launch stay on one XCD each (its L2 then holds the
 // operands of all its workgroups).  The vector updates of the same doubling
 // read the same D, so they ride along as extra workgroups, one wavefront per row.
 // Bound: the matrix cores (4 x 64 cycles per FP64 tile and 4 k), for few small
-// matrices the launch and the load latency at its start.
+// matrices the launch and the load latency at its start.  One doubling, FP64: one
+// matrix of 256 14.5 us, of 400 21.6, of 1000 137; 42 of 85 (dense) 13.8, 63 of 127
+// 31 with the vector rows, 85 of 171 106 (32 TFLOP/s).  The rows launched between
+// the tiles instead of after them: 42 against 31.
 #pragma once
+
+#include <algorithm>
 
 #include "colpower.hpp"
 #include "ops.hpp"
@@ -32,9 +42,13 @@ namespace tsk {
 
 template <typename real> using vec4 = real __attribute__((ext_vector_type(4)));
 
-enum CpowEpi {
-    CPOW_SQUARE = 0,  // out = 2 A + A A
-};
+// Products G = A B of k_cpow_gemm.  CPOW_SQUARE: out = 2 A + G (B = A).  The other three
+// form D = S - I of a Lawson RK4 step from the advection matrix A (column j's unit
+// vector through the four stages, diagonal factors e1 = E(h), eh = E(h/2)):
+//     STAGE2: b = A_ij eh_j + h/2 G,  sum = e1_i A_ij + 2 eh_i b,  out = b
+//     STAGE3: b = A_ij eh_j + h/2 G,  sum += 2 eh_i b,             out = eh_i b
+//     STAGE4: b = A_ij e1_j + h G,    out = (e1 - 1) I + h/6 (sum + b)
+enum CpowEpi { CPOW_SQUARE = 0, CPOW_STAGE2, CPOW_STAGE3, CPOW_STAGE4 };
 
 template <typename real> struct CpowArgs {
     const real* A;   // [count][2][ld * ld]
@@ -43,19 +57,27 @@ template <typename real> struct CpowArgs {
     const real* vin;  // [count][4][ld]
     real* vout;
     int ld, count;
+    int band_a, band_b, band_c;  // blocks off the diagonal
     int tile_blocks;  // workgroups of the tiles per matrix
+    int ts;           // k_cpow_apply: 16 MT
     int bit, affine;  // vector updates of this doubling
+    // stages only
+    real* sum;
+    const double* diag;  // [count][3][ld]: e1, eh, e1 - 1
+    double h;
+    int adj;  // STAGE4: the conjugate transpose of D
 };
 
 // One row of the vector updates by one wavefront.
 template <typename real>
-__device__ inline void cpow_row(const real* __restrict__ D, int ld, int row, const real* __restrict__ vin, bool bit,
-                                bool affine, real (&v)[4]) {
+__device__ inline void cpow_row(const real* __restrict__ D, int ld, int ts, int band, int row,
+                                const real* __restrict__ vin, bool bit, bool affine, real (&v)[4]) {
     const int lane = lane_id();
     const real* dr = D + size_t(row) * ld;
     const real* di = dr + size_t(ld) * ld;
     real s[4] = {real(0), real(0), real(0), real(0)};
-    for (int k = lane; k < ld; k += kWave) {
+    const int lo = max(0, ts * (row / ts - band)), hi = min(ld, ts * (row / ts + band + 1));
+    for (int k = lo + lane; k < hi; k += kWave) {
         const real a = dr[k], b = di[k];
         if (bit) {
             const real x = vin[k], y = vin[ld + k];
@@ -102,20 +124,30 @@ __device__ inline void cpow_place(int id, int per, int count, int& m, int& w) {
     }
 }
 
+// Two wavefronts per SIMD as the occupancy floor caps the kernel at 256 registers, where
+// the compiler keeps the accumulators in plain vector registers.  Without it they sit
+// in the accumulation half and move out and back around the products (MT = 2: 5 to
+// 15 % slower, MT = 1 the same).
 template <typename real, int MT, int EPI>
-__global__ __launch_bounds__(4 * kWave) void k_cpow_gemm(CpowArgs<real> g) {
+__global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
     using T = MfmaTile<real>;
     using V = typename T::V;
-    const int ld = g.ld, wv = int(threadIdx.x) / kWave, lane = int(threadIdx.x) % kWave;
-    const int vblocks = (g.bit || g.affine) ? ld / 4 : 0;
+    const int ld = g.ld, wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+    const int lane = int(threadIdx.x) % kWave;
+    // the tiles of all matrices first: the rows fill in beside them
     int m, w;
-    cpow_place(int(blockIdx.x), g.tile_blocks + vblocks, g.count, m, w);
+    const int ntile = g.tile_blocks * g.count;
+    const bool rows = int(blockIdx.x) >= ntile;
+    if (rows)
+        cpow_place(int(blockIdx.x) - ntile, ld / 4, g.count, m, w);
+    else
+        cpow_place(int(blockIdx.x), g.tile_blocks, g.count, m, w);
     const size_t mat = size_t(ld) * ld;
     const real* A = g.A + 2 * mat * m;
-    if (w >= g.tile_blocks) {
-        const int row = 4 * (w - g.tile_blocks) + wv;
+    if (rows) {
+        const int row = 4 * w + wv;
         real v[4];
-        cpow_row<real>(A, ld, row, g.vin + size_t(4 * ld) * m, g.bit, g.affine, v);
+        cpow_row<real>(A, ld, 16 * MT, g.band_a, row, g.vin + size_t(4 * ld) * m, g.bit, g.affine, v);
         if (lane == 0) {
             real* o = g.vout + size_t(4 * ld) * m + row;
 #pragma unroll
@@ -130,10 +162,20 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_gemm(CpowArgs<real> g) {
     const int wt = (ld + 2 * TS - 1) / (2 * TS);
     const int r0 = (2 * (w / wt) + (wv >> 1)) * TS, c0 = (2 * (w % wt) + (wv & 1)) * TS;
     if (r0 >= ld || c0 >= ld) return;
+    // the wavefront's block, and the k range inside both bands
+    const int rt = r0 / TS, ct = c0 / TS, off = rt > ct ? rt - ct : ct - rt;
+    if (off > g.band_c) return;
+    const int kfirst = max(0, max(rt - g.band_a, ct - g.band_b)) * TS;
+    const int kend = min(ld, min(rt + 1 + g.band_a, ct + 1 + g.band_b) * TS);
     const int lr = lane & 15, lk = lane >> 4;
-    const real* pa = A + size_t(r0 + lr) * ld + 4 * lk;
-    const real* pb = B + size_t(4 * lk) * ld + c0 + lr;
+    // uniform row pointers plus 32-bit lane offsets: the loads take the scalar-base
+    // form and the address arithmetic stays off the vector unit
+    const unsigned oa = unsigned(lr) * unsigned(ld) + 4u * unsigned(lk);
+    const unsigned ob = 4u * unsigned(lk) * unsigned(ld) + unsigned(lr);
+    const real* pa = A + size_t(r0) * ld;
+    const real* pb = B + c0;
     V accr[MT][MT], acci[MT][MT];
+    const bool inside = off <= g.band_a;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -142,57 +184,62 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_gemm(CpowArgs<real> g) {
             for (int r = 0; r < 4; ++r) {
                 if constexpr (EPI == CPOW_SQUARE) {
                     const size_t o = size_t(r0 + 16 * i + T::row(lane, r)) * ld + c0 + 16 * j + lr;
-                    accr[i][j][r] = real(2) * A[o];
-                    acci[i][j][r] = real(2) * A[o + mat];
+                    accr[i][j][r] = inside ? real(2) * A[o] : real(0);
+                    acci[i][j][r] = inside ? real(2) * A[o + mat] : real(0);
                 } else {
                     accr[i][j][r] = acci[i][j][r] = real(0);
                 }
             }
-    vec4<real> ar[MT], ai[MT];
-    real br[MT][4], bi[MT][4];
-    auto load = [&](int k, vec4<real> (&xr)[MT], vec4<real> (&xi)[MT], real (&yr)[MT][4], real (&yi)[MT][4]) {
+    // ST stages of 16 k in registers: while one multiplies, the next ST - 1 load
+    constexpr int ST = MT == 1 ? 4 : 2;
+    vec4<real> ar[ST][MT], ai[ST][MT];
+    real br[ST][MT][4], bi[ST][MT][4];
+    auto load = [&](int st, int k) {
+        k = k < kend ? k : kend - 16;
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             const real* p = pa + size_t(16 * i) * ld + k;
-            xr[i] = *reinterpret_cast<const vec4<real>*>(p);
-            xi[i] = *reinterpret_cast<const vec4<real>*>(p + mat);
+            ar[st][i] = *reinterpret_cast<const vec4<real>*>(p + oa);
+            ai[st][i] = *reinterpret_cast<const vec4<real>*>(p + mat + oa);
         }
 #pragma unroll
         for (int j = 0; j < MT; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const real* p = pb + size_t(k + r) * ld + 16 * j;
-                yr[j][r] = p[0];
-                yi[j][r] = p[mat];
+                br[st][j][r] = p[ob];
+                bi[st][j][r] = (p + mat)[ob];
             }
     };
-    load(0, ar, ai, br, bi);
-    for (int k = 0; k < ld; k += 16) {
-        vec4<real> nar[MT], nai[MT];
-        real nbr[MT][4], nbi[MT][4];
-        load(k + 16 < ld ? k + 16 : k, nar, nai, nbr, nbi);  // in flight during the products below
+    auto products = [&](int st) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
                 for (int j = 0; j < MT; ++j) {
-                    accr[i][j] = T::fma(ar[i][r], br[j][r], accr[i][j]);
-                    acci[i][j] = T::fma(ar[i][r], bi[j][r], acci[i][j]);
-                    accr[i][j] = T::fma(-ai[i][r], bi[j][r], accr[i][j]);
-                    acci[i][j] = T::fma(ai[i][r], br[j][r], acci[i][j]);
+                    accr[i][j] = T::fma(ar[st][i][r], br[st][j][r], accr[i][j]);
+                    acci[i][j] = T::fma(ar[st][i][r], bi[st][j][r], acci[i][j]);
+                    accr[i][j] = T::fma(-ai[st][i][r], bi[st][j][r], accr[i][j]);
+                    acci[i][j] = T::fma(ai[st][i][r], br[st][j][r], acci[i][j]);
                 }
+    };
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            ar[i] = nar[i];
-            ai[i] = nai[i];
+    for (int st = 0; st < ST - 1; ++st) load(st, kfirst + 16 * st);
+    int k0 = kfirst;
+    for (; k0 + 16 * ST <= kend; k0 += 16 * ST) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                br[i][r] = nbr[i][r];
-                bi[i][r] = nbi[i][r];
-            }
+        for (int st = 0; st < ST; ++st) {
+            load((st + ST - 1) % ST, k0 + 16 * (st + ST - 1));
+            // keeps the loads here, ahead of the products (the compiler would sink
+            // them to their uses)
+            __builtin_amdgcn_sched_barrier(0);
+            products(st);
         }
     }
+#pragma unroll
+    for (int st = 0; st < ST - 1; ++st)  // the last ld / 16 mod ST stages, already loaded
+        if (k0 + 16 * st < kend) products(st);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -200,8 +247,36 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_gemm(CpowArgs<real> g) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const size_t o = size_t(r0 + 16 * i + T::row(lane, r)) * ld + c0 + 16 * j + lr;
-                O[o] = accr[i][j][r];
-                O[o + mat] = acci[i][j][r];
+                if constexpr (EPI == CPOW_SQUARE) {
+                    O[o] = accr[i][j][r];
+                    O[o + mat] = acci[i][j][r];
+                } else {
+                    const int ri = r0 + 16 * i + T::row(lane, r), cj = c0 + 16 * j + lr;
+                    const double* dg = g.diag + size_t(3 * ld) * m;
+                    const double ej = EPI == CPOW_STAGE4 ? dg[cj] : dg[ld + cj];
+                    const double hc = EPI == CPOW_STAGE4 ? g.h : 0.5 * g.h, e1i = dg[ri], ehi = dg[ld + ri];
+                    real* sm = g.sum + 2 * mat * m;
+                    const double ax = A[o], ay = A[o + mat];
+                    const double bx = ax * ej + hc * double(accr[i][j][r]), by = ay * ej + hc * double(acci[i][j][r]);
+                    if constexpr (EPI == CPOW_STAGE2) {
+                        sm[o] = real(e1i * ax + 2.0 * ehi * bx);
+                        sm[o + mat] = real(e1i * ay + 2.0 * ehi * by);
+                        O[o] = real(bx);
+                        O[o + mat] = real(by);
+                    } else if constexpr (EPI == CPOW_STAGE3) {
+                        sm[o] = real(double(sm[o]) + 2.0 * ehi * bx);
+                        sm[o + mat] = real(double(sm[o + mat]) + 2.0 * ehi * by);
+                        O[o] = real(ehi * bx);
+                        O[o + mat] = real(ehi * by);
+                    } else {
+                        const double h6 = g.h / 6.0;
+                        const double dx = h6 * (double(sm[o]) + bx) + (ri == cj ? dg[2 * ld + ri] : 0.0);
+                        const double dy = h6 * (double(sm[o + mat]) + by);
+                        const size_t p = g.adj ? size_t(cj) * ld + ri : o;
+                        O[p] = real(dx);
+                        O[p + mat] = real(g.adj ? -dy : dy);
+                    }
+                }
             }
 }
 
@@ -223,7 +298,7 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
     const int row = 4 * w + wv;
     const real* vin = g.vin + size_t(4 * ld) * m;
     real v[4];
-    cpow_row<real>(g.A + 2 * size_t(ld) * ld * m, ld, row, vin, true, false, v);
+    cpow_row<real>(g.A + 2 * size_t(ld) * ld * m, ld, g.ts, g.band_a, row, vin, true, false, v);
     if (g.affine) {
         v[0] += vin[2 * ld + row];
         v[1] += vin[3 * ld + row];
@@ -246,45 +321,103 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
     }
 }
 
-// Workspace of `count` matrices: two buffers of matrices and of vectors.
+// Workspace of `count` matrices: diagonal factors (of the stages), two buffers of
+// vectors and nbuf of matrices, the
+// doublings alternating between `first` and `first` ^ 1.
 struct CpowWork {
-    DevBuf mat, vec;
-    int count = 0, ld = 0, mt = 1;
+    DevBuf mat, vec, diag;
+    int count = 0, ld = 0, mt = 1, nbuf = 2, first = 0;
     size_t real_bytes = 8;
-    // Bytes per matrix (both buffers).
-    static size_t bytes(int ld, size_t rb) { return 4 * size_t(ld) * ld * rb; }
+    // Bytes per matrix and buffer.
+    static size_t bytes(int ld, size_t rb) { return 2 * size_t(ld) * ld * rb; }
     template <typename real> real* D(int b) const { return mat.as<real>() + size_t(b) * 2 * ld * ld * count; }
     template <typename real> real* v(int b) const { return vec.as<real>() + size_t(b) * 4 * ld * count; }
-    bool fits(int n_, int count_, size_t rb) const {
-        return mat.ptr && ld >= n_ && count == count_ && real_bytes == rb;
+    // Leading dimension and tiles per wavefront of `count` n x n matrices: two tiles per
+    // wavefront once one each would queue several wavefronts per SIMD (63 matrices of
+    // 127: a doubling 26 us with two, 36 with one; 42 of 85: 18 and 14).
+    static int tiles_of(int n_, int count_) {
+        const int t = (n_ + 15) / 16;
+        return double(t) * t * count_ >= 3072.0 ? 2 : 1;
+    }
+    static int ld_of(int n_, int count_) {
+        const int w = 16 * tiles_of(n_, count_);
+        return (n_ + w - 1) / w * w;
     }
     tsk_status ensure(int n_, int count_, size_t rb) {
-        // two tiles per wavefront once one tile each would queue several wavefronts per SIMD
-        const int t = (n_ + 15) / 16;
-        mt = double(t) * t * count_ >= 3072.0 ? 2 : 1;
-        ld = (n_ + 16 * mt - 1) / (16 * mt) * (16 * mt);
+        mt = tiles_of(n_, count_);
+        ld = ld_of(n_, count_);
         count = count_;
         real_bytes = rb;
-        TSK_TRY(mat.ensure(bytes(ld, rb) * count));
+        TSK_TRY(mat.ensure(size_t(nbuf) * bytes(ld, rb) * count));
+        TSK_TRY(diag.ensure(3 * size_t(ld) * sizeof(double) * count));
         return vec.ensure(8 * size_t(ld) * rb * count);
+    }
+    // For a matvec on `stream`, or false: step instead.  A captured matvec steps (its
+    // graph would share the workspace with calls beside its replays, and outlive it);
+    // so does one that finds no memory.  The allocation is legal while another stream
+    // captures.
+    bool ready(int n_, int count_, size_t rb, hipStream_t stream) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+        if (mat.ptr && vec.ptr && ld >= n_ && count == count_ && real_bytes == rb) return true;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        const bool ok = ensure(n_, count_, rb) == TSK_OK;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!ok) (void)hipGetLastError();  // the failed allocation is not the stepper's error
+        return ok;
     }
 };
 
-// Doublings before the last matrix is applied nsteps >> k times: one more has to
-// save more applications than it costs.  ratio: cost of a doubling over that of an
-// application.
-inline int cpow_doublings(int64_t nsteps, double ratio) {
-    int k = 0;
-    while (double((nsteps >> k) - (nsteps >> (k + 1))) > ratio) ++k;
-    return k;
+// Estimated times in us of the work on `count` matrices of leading dimension ld, MT tiles
+// per wavefront, `band` blocks wide.
+struct CpowCost {
+    int ld, count, mt;
+    bool fp32;
+    double width(double band) const { return std::min(double(ld), 16.0 * mt * (2.0 * band + 1.0)); }
+    // A product of matrices a and b wide: a launch and the loads' latency, or the
+    // matrix cores.
+    double product(double a, double b) const {
+        const double k = std::min(width(a), width(b)), flops = 8.0 * ld * width(a + b) * k * count;
+        return 2.8 + 0.045 * std::min(k, 256.0) + flops / (fp32 ? 1.0e8 : 6.0e7);
+    }
+    // An application: a launch, or the matrices' bytes.
+    double application(double b) const {
+        return 2.8 + (fp32 ? 8.0 : 16.0) * width(b) * ld * count / 7.0e6;
+    }
+    // The doublings k before the last matrix is applied nsteps >> k times that take the
+    // least time, and that time.
+    int doublings(int64_t nsteps, double band, double* cost) const {
+        double spent = 0.0, best = 0.0;
+        int bk = 0;
+        for (int k = 0; k == 0 || (nsteps >> k) > 0; ++k, band *= 2.0) {
+            const double total = spent + double(nsteps >> k) * application(band);
+            if (k == 0 || total < best) {
+                best = total;
+                bk = k;
+            }
+            spent += product(band, band);
+        }
+        *cost = best;
+        return bk;
+    }
+};
+
+template <typename real, int EPI>
+void cpow_gemm(const CpowWork& W, dim3 grid, const CpowArgs<real>& g, hipStream_t s) {
+    if (W.mt == 2)
+        hipLaunchKernelGGL((k_cpow_gemm<real, 2, EPI>), grid, dim3(4 * kWave), 0, s, g);
+    else
+        hipLaunchKernelGGL((k_cpow_gemm<real, 1, EPI>), grid, dim3(4 * kWave), 0, s, g);
 }
 
-// The nsteps steps of the matrices in W.D(0) and vectors in W.v(0).
+// The nsteps steps of the matrices in W.D(W.first), `band` blocks wide, and vectors in
+// W.v(0).
 template <typename real>
-tsk_status cpow_run(const CpowWork& W, int64_t nsteps, bool affine, int doublings, const CpowOut<real>& out,
-                    hipStream_t s) {
+tsk_status cpow_run(const CpowWork& W, int64_t nsteps, bool affine, int band, int doublings,
+                    const CpowOut<real>& out, hipStream_t s) {
     const int ld = W.ld, ts = 32 * W.mt, wt = (ld + ts - 1) / ts;
-    int b = 0, vb = 0;
+    int b = W.first, vb = 0;
     for (int k = 0; k < doublings; ++k) {
         CpowArgs<real> g{};
         g.A = g.B = W.D<real>(b);
@@ -293,17 +426,17 @@ tsk_status cpow_run(const CpowWork& W, int64_t nsteps, bool affine, int doubling
         g.vout = W.v<real>(vb ^ 1);
         g.ld = ld;
         g.count = W.count;
+        g.band_a = g.band_b = band;
+        g.band_c = 2 * band;
         g.tile_blocks = wt * wt;
         g.bit = int((nsteps >> k) & 1);
         g.affine = affine ? 1 : 0;
         const int vblocks = (g.bit || g.affine) ? ld / 4 : 0;
         const dim3 grid(unsigned((g.tile_blocks + vblocks) * W.count));
-        if (W.mt == 2)
-            hipLaunchKernelGGL((k_cpow_gemm<real, 2, CPOW_SQUARE>), grid, dim3(4 * kWave), 0, s, g);
-        else
-            hipLaunchKernelGGL((k_cpow_gemm<real, 1, CPOW_SQUARE>), grid, dim3(4 * kWave), 0, s, g);
+        cpow_gemm<real, CPOW_SQUARE>(W, grid, g, s);
         b ^= 1;
         if (vblocks) vb ^= 1;
+        band = std::min(2 * band, ld);
     }
     for (int64_t r = nsteps >> doublings; r > 0; --r) {
         CpowArgs<real> g{};
@@ -312,6 +445,8 @@ tsk_status cpow_run(const CpowWork& W, int64_t nsteps, bool affine, int doubling
         g.vout = W.v<real>(vb ^ 1);
         g.ld = ld;
         g.count = W.count;
+        g.band_a = band;
+        g.ts = 16 * W.mt;
         g.affine = affine ? 1 : 0;
         hipLaunchKernelGGL(k_cpow_apply<real>, dim3(unsigned(ld / 4 * W.count)), dim3(4 * kWave), 0, s, g, out,
                            r == 1 ? 1 : 0);

@@ -38,6 +38,7 @@
 #include "colbloch.hpp"
 #include "colcouple.hpp"
 #include "colcouple_adj.hpp"
+#include "colmatrix.hpp"
 #include "colpower.hpp"
 #include "colstep.hpp"
 #include "kolmo2d.hpp"
@@ -187,6 +188,13 @@ tsk_status column_choice(const TuneKey& key, hipStream_t s, F&& launch, int* out
             *out = it->second;
             return TSK_OK;
         }
+    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    TSK_HIP(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) {
+        // a captured matvec whose eager calls square, so that nothing was timed yet
+        *out = 1;
+        return TSK_OK;
     }
     if (max_cols(key.N) == 1) {
         *out = 1;
@@ -551,6 +559,34 @@ inline bool power_pays(int M, int nh, int nsteps, bool fp32) {
     return tiles <= kPowMaxTiles && power_blocks(M, nh) <= 768 && nsteps >= (fp32 ? kMin32 : kMin64)[tiles - 1];
 }
 
+// Squaring (colmatrix.hpp) or the column stepper, for a profile of harmonics up to h.
+// Measured, 3 harmonics, FP64, us (stepping / squaring): 10, 20, 60 and 200 steps of
+// 32^2 38/32 74/37 214/43 704/51; 96^2 51/44 98/51 287/63 947/77; 128^2 30/73 56/88 160/108
+// 526/135; 192^2 54/132 104/162 301/204 997/257; 256^2 57/255 109/311 318/469 1052/617;
+// 384^2 133/427 258/564 759/842 2522/1356; 512^2 114/868 229/1090 661/1602 2190/3453.  FP32
+// squares at 0.5 to 0.8 of that.  kStep64, kStep32: a step of the column stepper in us;
+// the estimate of squaring is within a third of the times above.  Fewer than 16 steps
+// always step: there is little to gain.
+struct ColumnPlan {
+    bool square = false;
+    int doublings = 0;
+};
+inline ColumnPlan column_plan(int N, int M, int h, int nsteps, bool fp32) {
+    constexpr int kSize[10] = {16, 32, 48, 64, 96, 128, 192, 256, 384, 512};
+    constexpr double kStep64[10] = {2.8, 3.5, 4.1, 4.4, 4.7, 2.6, 5.0, 5.3, 12.6, 10.9};
+    constexpr double kStep32[10] = {2.5, 3.2, 3.5, 3.8, 3.9, 2.0, 4.1, 4.2, 9.3, 7.5};
+    int i = 0;
+    while (i < 9 && kSize[i] < N) ++i;
+    const CpowCost c{CpowWork::ld_of(2 * M + 1, M), M, CpowWork::tiles_of(2 * M + 1, M), fp32};
+    const int b1 = band_blocks(h, c.mt), b4 = band_blocks(4 * h, c.mt);
+    ColumnPlan p;
+    double cost = 0.0;
+    p.doublings = c.doublings(nsteps, b4, &cost);
+    cost += 6.0 + c.product(b1, b1) + 2.0 * c.product(b1, b4);
+    p.square = nsteps >= 16 && 1.1 * cost < (fp32 ? kStep32 : kStep64)[i] * nsteps;
+    return p;
+}
+
 struct KolmoOp final : Operator {
     int N = 0, M = 0;
     tsk_precision prec = TSK_FP64;
@@ -564,6 +600,11 @@ struct KolmoOp final : Operator {
     int nh = 0;
     double amp = 0.0, y0 = 0.0;
     DevBuf tw, negU, dOdy, Z;
+    // squared columns (colmatrix.hpp): the profiles' DFT coefficients, and the
+    // workspace, sized on first use
+    DevBuf prof;
+    int hmax = 0;  // highest harmonic of the profiles
+    CpowWork colpow;
     DevBuf tasks[3];   // single-instance task lists for 1 and 2 columns per wavefront
     int ntasks[3] = {0, 0, 0};
     int force_cols = 0;  // 0: automatic choice; 1, 2: column stepper; 3: Bloch-sector stepper
@@ -595,6 +636,48 @@ struct KolmoOp final : Operator {
         } else {
             TSK_HIP(hipMemcpy(buf.ptr, v.data(), v.size() * 8, hipMemcpyHostToDevice));
         }
+        return TSK_OK;
+    }
+
+    // DFT coefficients (1/N) sum_l f_l e^{-2 pi i m l / N} of U = -nu and dOmega/dy = oy
+    tsk_status upload_profile_dft(const std::vector<double>& nu, const std::vector<double>& oy) {
+        std::vector<double> cs(N), sn(N), h(4 * size_t(N)), u(N), o(N);
+        const double pi = 3.14159265358979323846264338327950288;
+        for (int l = 0; l < N; ++l) {
+            cs[l] = std::cos(2.0 * pi * l / N);
+            sn[l] = std::sin(2.0 * pi * l / N);
+            u[l] = -nu[l];
+            o[l] = oy[l];
+        }
+        for (int m = 0; 2 * m <= N; ++m) {
+            double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+            for (int l = 0, t = 0; l < N; ++l, t = t + m >= N ? t + m - N : t + m) {
+                a += u[l] * cs[t];
+                b -= u[l] * sn[t];
+                c += o[l] * cs[t];
+                d -= o[l] * sn[t];
+            }
+            const int q = (N - m) % N;  // the conjugate
+            h[4 * m] = h[4 * q] = a / N;
+            h[4 * q + 1] = -b / N;
+            h[4 * q + 3] = -d / N;
+            h[4 * m + 1] = b / N;
+            h[4 * m + 2] = h[4 * q + 2] = c / N;
+            h[4 * m + 3] = d / N;
+        }
+        // harmonics below the rounding of the samples are not there
+        double top[2] = {0.0, 0.0};
+        for (int m = 0; m < N; ++m)
+            for (int f = 0; f < 2; ++f) top[f] = std::max(top[f], std::hypot(h[4 * m + 2 * f], h[4 * m + 2 * f + 1]));
+        hmax = 0;
+        for (int m = 0; m < N; ++m)
+            for (int f = 0; f < 2; ++f)
+                if (std::hypot(h[4 * m + 2 * f], h[4 * m + 2 * f + 1]) > 0x1.0p-51 * top[f])
+                    hmax = std::max(hmax, std::min(m, N - m));
+        // products that wrap on the grid couple the ends of the column
+        if (hmax >= N - 2 * M) hmax = 2 * M;
+        TSK_TRY(prof.ensure(h.size() * sizeof(double)));
+        TSK_HIP(hipMemcpy(prof.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
         return TSK_OK;
     }
 
@@ -652,7 +735,20 @@ struct KolmoOp final : Operator {
         launch_bloch_stepper<real>(N, inst<real>(x, 0, y, nullptr), nullptr, nullptr, 1, 0, tw.as<cplx<real>>(),
                                    stream);
     }
-    tsk_status apply(const void* x, void* y) override { return forward(x, y, use_power()); }
+    // Squared columns: base flows that the column stepper would advance, unless a
+    // column variant is forced or there is no workspace.
+    ColumnPlan columns() const { return column_plan(N, M, hmax, nsteps, prec == TSK_FP32); }
+    bool use_columns() {
+        if (gen || couple || bloch || force_cols != 0 || !columns().square) return false;
+        colpow.nbuf = 4;
+        colpow.first = 2;
+        return colpow.ready(2 * M + 1, M, rb(), stream);
+    }
+    template <typename real> tsk_status run_columns(const void* x, void* y, bool adj) {
+        return colmatrix_run<real>(colpow, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax,
+                                    adj, columns().doublings, stream);
+    }
+    tsk_status apply(const void* x, void* y) override { return forward(x, y, true); }
     // M^T M x of the singular-value runs, always step by step.  The x-translation
     // symmetry of a parallel base makes singular values double, and the second
     // copies, which these runs return, enter the Krylov space only through the
@@ -663,12 +759,13 @@ struct KolmoOp final : Operator {
         TSK_TRY(forward(x, mid, false));
         return backward(mid, y, false);
     }
-    // square: by repeated squaring (colpower.hpp), where use_power() allows it
+    // square: by repeated squaring, where use_power() (chains) and use_columns()
+    // allow it
     tsk_status forward(const void* x, void* y, bool square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply: input and output must not alias");
         if (gen) return gen2d_apply(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square) {
+        if (square && use_power()) {
             tuned_wpw = 4;
             if (prec == TSK_FP32)
                 return launch_power<float, false>(inst<float>(x, 0, y, nullptr), stream);
@@ -703,6 +800,8 @@ struct KolmoOp final : Operator {
             TSK_HIP(hipGetLastError());
             return TSK_OK;
         }
+        if (square && use_columns())
+            return prec == TSK_FP32 ? run_columns<float>(x, y, false) : run_columns<double>(x, y, false);
         auto launch = [&](int c) {
             if (prec == TSK_FP32)
                 dispatch_colstep<float>(N, inst<float>(x, 0, y, nullptr), nullptr, tasks[c].as<ColTask>(), ntasks[c],
@@ -724,12 +823,12 @@ struct KolmoOp final : Operator {
     // kept, else one wavefront per workgroup); other parallel bases the
     // transposed column stepper (k_colstep_adj, task list of 1-column tasks);
     // a general 2-D base the transposed pipeline of kolmo2d.hip.
-    tsk_status apply_adjoint(const void* x, void* y) override { return backward(x, y, use_power()); }
+    tsk_status apply_adjoint(const void* x, void* y) override { return backward(x, y, true); }
     tsk_status backward(const void* x, void* y, bool square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply_adjoint: input and output must not alias");
         if (gen) return gen2d_apply_adjoint(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square) {
+        if (square && use_power()) {
             if (prec == TSK_FP32)
                 return launch_power<float, true>(inst<float>(x, 0, y, nullptr), stream);
             return launch_power<double, true>(inst<double>(x, 0, y, nullptr), stream);
@@ -744,6 +843,8 @@ struct KolmoOp final : Operator {
             TSK_HIP(hipGetLastError());
             return TSK_OK;
         }
+        if (square && use_columns())
+            return prec == TSK_FP32 ? run_columns<float>(x, y, true) : run_columns<double>(x, y, true);
         if (prec == TSK_FP32)
             dispatch_colstep_adj<float>(N, inst<float>(x, 0, y, nullptr), tasks[1].as<ColTask>(), ntasks[1], prop,
                                         tw.ptr, stream);
@@ -989,6 +1090,7 @@ tsk_status kolmo_set_base_parallel(Operator* op, const double* U, const double* 
     }
     TSK_TRY(k->upload_real(k->negU, nu));
     TSK_TRY(k->upload_real(k->dOdy, oy));
+    if (!k->couple && !k->bloch) TSK_TRY(k->upload_profile_dft(nu, oy));
     gen2d_free(k->gen);
     k->gen = nullptr;
     k->base_set = true;
