@@ -147,6 +147,14 @@ tsk_status tsk_get_tuning(tsk_op op, int* columns_per_wave) {
     })
 }
 
+// Not in the header: lets the tests take the path of a wait that gave up.
+__attribute__((visibility("default"))) int tskx_flow_polls(tsk_op op, int polls) {
+    TSK_GUARD({
+        TSK_NEED(op);
+        return kolmo_set_flow_polls(op->op.get(), polls);
+    })
+}
+
 tsk_status tsk_set_stepper_waves(tsk_op op, int waves_per_group) {
     TSK_GUARD({
         TSK_NEED(op);

@@ -156,4 +156,35 @@ __device__ inline C* fft_lds(C* a, C* b, const C* tw, int tid) {
     return fft_passes<N, 0, 1, SIGN, NT>(a, b, tw, tid);
 }
 
+// The transform by one wavefront alone: passes ordered by the wavefront itself, no
+// workgroup barrier (LDS operations of one wavefront complete in order).  Radix 4
+// before 8: one wavefront's time is the length of its longest lane, and a radix-8
+// pass of 128 points keeps 16 lanes busy with twice the work of radix 4 on 32.
+constexpr int fft_wave_radix(int N, int pass) {
+    int p = 0;
+    while (N % 4 == 0) { if (p == pass) return 4; N /= 4; ++p; }
+    if (N % 2 == 0) { if (p == pass) return 2; N /= 2; ++p; }
+    while (N % 3 == 0) { if (p == pass) return 3; N /= 3; ++p; }
+    return 1;
+}
+constexpr int fft_wave_num_passes(int N) {
+    int p = 0;
+    while (fft_wave_radix(N, p) > 1) ++p;
+    return p;
+}
+template <int N, int P, int NS, int SIGN, typename C>
+__device__ inline C* fft_wave_passes(C* a, C* b, const C* tw, int lane) {
+    if constexpr (P >= fft_wave_num_passes(N)) {
+        return a;
+    } else {
+        constexpr int R = fft_wave_radix(N, P);
+        fft_pass<N, R, NS, SIGN, kWave>(a, b, tw, lane);
+        wave_lds_sync();
+        return fft_wave_passes<N, P + 1, NS * R, SIGN>(b, a, tw, lane);
+    }
+}
+template <int N, int SIGN, typename C> __device__ inline C* fft_wave(C* a, C* b, const C* tw, int lane) {
+    return fft_wave_passes<N, 0, 1, SIGN>(a, b, tw, lane);
+}
+
 }  // namespace tsk

@@ -1160,6 +1160,14 @@ tsk_status kolmo_get_stepper_waves(const Operator* op, int* w) {
     return TSK_OK;
 }
 
+tsk_status kolmo_set_flow_polls(Operator* op, int polls) {
+    auto* k = dynamic_cast<KolmoOp*>(op);
+    if (!k) return fail(TSK_EINVAL, "not a Navier-Stokes operator");
+    for (Gen2D* g : {k->gen, k->nlw})
+        if (g) gen2d_set_polls(g, polls);
+    return TSK_OK;
+}
+
 bool kolmo_parallel(const Operator* op) {
     const auto* k = dynamic_cast<const KolmoOp*>(op);
     return k && !k->gen;

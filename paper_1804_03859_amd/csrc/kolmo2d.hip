@@ -23,7 +23,8 @@
 // the row kernel reads the four base fields.  Running the four inverse
 // transforms of a workgroup concurrently keeps the dependent chain of each
 // kernel at two transforms.  The x- and y-transforms are the Stockham LDS FFTs
-// of fft.hpp.
+// of fft.hpp.  Up to 256^2 the integrations keep both kinds of workgroup resident in
+// one launch (genflow.hpp); the stage kernels run the larger grids.
 //
 // Scaling.  Packed coefficients c = sqrt(2) rfft2(omega)/N^2.  The derived
 // fields are formed from c directly and the transforms are unnormalised, so
@@ -33,6 +34,7 @@
 #include <vector>
 
 #include "fft.hpp"
+#include "genflow.hpp"
 #include "kolmo2d.hpp"
 #include "ops.hpp"
 
@@ -74,17 +76,16 @@ enum GenMode { GEN_FIRST = 0, GEN_STAGE = 1, GEN_LAST = 2 };
 // then forms derived field f and runs its inverse transform, the four
 // concurrently.
 template <typename real, int N>
-__global__ __launch_bounds__(kGT) void k_gen_col(const real* __restrict__ xin, real* __restrict__ W,
-                                                 real* __restrict__ Acc, const cplx<real>* __restrict__ Q,
-                                                 cplx<real>* __restrict__ Gf, real* __restrict__ yout,
-                                                 const cplx<real>* __restrict__ twg, double alpha, double Re,
-                                                 double dt, int q, int mode, const real* __restrict__ fvec) {
+__device__ inline void gen_col(int kx, const real* __restrict__ xin, real* __restrict__ W, real* __restrict__ Acc,
+                               const cplx<real>* __restrict__ Q, cplx<real>* __restrict__ Gf,
+                               real* __restrict__ yout, const cplx<real>* __restrict__ twg, double alpha, double Re,
+                               double dt, int q, int mode, const real* __restrict__ fvec) {
     using C = cplx<real>;
     using G = Geo2<N>;
     constexpr int M = G::M, MC = G::MC, NM = G::NM;
     __shared__ C sA[4][N], sB[4][N], sT[N];
     __shared__ C sS[NM];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, kx = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int nq = kx == 0 ? M : NM;  // packed complex entries of the column
     const int64_t base = G::seg(kx);
     for (int t = tid; t < N; t += kGT) sT[t] = twg[t];
@@ -185,6 +186,14 @@ __global__ __launch_bounds__(kGT) void k_gen_col(const real* __restrict__ xin, r
     C* out = Gf + (size_t(wv) * MC + kx) * N;
     for (int t = lane; t < N; t += kWave) out[t] = X[t];
 }
+template <typename real, int N>
+__global__ __launch_bounds__(kGT) void k_gen_col(const real* __restrict__ xin, real* __restrict__ W,
+                                                 real* __restrict__ Acc, const cplx<real>* __restrict__ Q,
+                                                 cplx<real>* __restrict__ Gf, real* __restrict__ yout,
+                                                 const cplx<real>* __restrict__ twg, double alpha, double Re,
+                                                 double dt, int q, int mode, const real* __restrict__ fvec) {
+    gen_col<real, N>(int(blockIdx.x), xin, W, Acc, Q, Gf, yout, twg, alpha, Re, dt, q, mode, fvec);
+}
 
 // Row kernel, one workgroup per RPW consecutive grid rows y0 .. y0 + RPW - 1
 // (gen_rows_per_group).  Wavefront 2r + pr
@@ -208,10 +217,9 @@ template <typename real, int N> constexpr int gen_rows_per_group() {
     return 2;
 }
 template <typename real, int N, int RM, int RPW>
-__global__ __launch_bounds__(2 * RPW * kWave) void k_gen_row(const cplx<real>* __restrict__ Gf, real* __restrict__ U,
-                                                             real* __restrict__ V, real* __restrict__ Ox,
-                                                             real* __restrict__ Oy, cplx<real>* __restrict__ Q,
-                                                             const cplx<real>* __restrict__ twg, double U0) {
+__device__ inline void gen_row(int y0, const cplx<real>* __restrict__ Gf, real* __restrict__ U,
+                               real* __restrict__ V, real* __restrict__ Ox, real* __restrict__ Oy,
+                               cplx<real>* __restrict__ Q, const cplx<real>* __restrict__ twg, double U0) {
     using C = cplx<real>;
     using G = Geo2<N>;
     constexpr int M = G::M, MC = G::MC;
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(2 * RPW * kWave) void k_gen_row(const cplx<real>* _
     __shared__ C sT[N];
     __shared__ C sA[2 * RPW][N], sB[2 * RPW][N];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int y0 = RPW * xcd_row_group(blockIdx.x, gridDim.x), r = wv >> 1, pr = wv & 1, y = y0 + r;
+    const int r = wv >> 1, pr = wv & 1, y = y0 + r;
     // the base fields of the thread's grid points (ROW_LIN), loaded first so that
     // their latency overlaps the transforms; point e = rr N + x of the workgroup
     real bU[RX], bV[RX], bOx[RX], bOy[RX];
@@ -302,6 +310,13 @@ __global__ __launch_bounds__(2 * RPW * kWave) void k_gen_row(const cplx<real>* _
         Q[size_t(k) * N + y0 + 2 * g + 1] = cmk<C>(real(0.5) * (za.y - zb.y), real(-0.5) * (za.x - zb.x));
     }
 }
+template <typename real, int N, int RM, int RPW>
+__global__ __launch_bounds__(2 * RPW * kWave) void k_gen_row(const cplx<real>* __restrict__ Gf, real* __restrict__ U,
+                                                             real* __restrict__ V, real* __restrict__ Ox,
+                                                             real* __restrict__ Oy, cplx<real>* __restrict__ Q,
+                                                             const cplx<real>* __restrict__ twg, double U0) {
+    gen_row<real, N, RM, RPW>(RPW * xcd_row_group(blockIdx.x, gridDim.x), Gf, U, V, Ox, Oy, Q, twg, U0);
+}
 
 // ---- the transposed pipeline (discrete adjoint) ------------------------------------
 // The advection operator of a stage is N s = -R sum_f B_f P(D_f s): D_f the four
@@ -329,17 +344,17 @@ __global__ __launch_bounds__(2 * RPW * kWave) void k_gen_row(const cplx<real>* _
 // q (W holds z, Acc acc), the next stage input.  LAST (stage 3 of the last
 // step): y = new z.
 template <typename real, int N>
-__global__ __launch_bounds__(kGT) void k_gen_col_adj(const real* __restrict__ xin, real* __restrict__ W,
-                                                     real* __restrict__ Acc, const cplx<real>* __restrict__ Q4,
-                                                     cplx<real>* __restrict__ G1, real* __restrict__ yout,
-                                                     const cplx<real>* __restrict__ twg, double alpha, double Re,
-                                                     double dt, int q, int mode) {
+__device__ inline void gen_col_adj(int kx, const real* __restrict__ xin, real* __restrict__ W,
+                                   real* __restrict__ Acc, const cplx<real>* __restrict__ Q4,
+                                   cplx<real>* __restrict__ G1, real* __restrict__ yout,
+                                   const cplx<real>* __restrict__ twg, double alpha, double Re, double dt, int q,
+                                   int mode) {
     using C = cplx<real>;
     using G = Geo2<N>;
     constexpr int M = G::M, MC = G::MC, NM = G::NM;
     __shared__ C sA[4][N], sB[4][N], sT[N];
     __shared__ C sS[NM];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, kx = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int nq = kx == 0 ? M : NM;  // packed complex entries of the column
     const int64_t base = G::seg(kx);
     for (int t = tid; t < N; t += kGT) sT[t] = twg[t];
@@ -441,6 +456,14 @@ __global__ __launch_bounds__(kGT) void k_gen_col_adj(const real* __restrict__ xi
     C* out = G1 + size_t(kx) * N;
     for (int t = tid; t < N; t += kGT) out[t] = X[t];
 }
+template <typename real, int N>
+__global__ __launch_bounds__(kGT) void k_gen_col_adj(const real* __restrict__ xin, real* __restrict__ W,
+                                                     real* __restrict__ Acc, const cplx<real>* __restrict__ Q4,
+                                                     cplx<real>* __restrict__ G1, real* __restrict__ yout,
+                                                     const cplx<real>* __restrict__ twg, double alpha, double Re,
+                                                     double dt, int q, int mode) {
+    gen_col_adj<real, N>(int(blockIdx.x), xin, W, Acc, Q4, G1, yout, twg, alpha, Re, dt, q, mode);
+}
 
 // Row kernel of the transposed pipeline, one workgroup per pair of grid rows
 // (y0, y0 + 1): the inverse x-transform of both rows of v (packed as a + i b),
@@ -448,10 +471,10 @@ __global__ __launch_bounds__(kGT) void k_gen_col_adj(const real* __restrict__ xi
 // x-transform of field f of both rows (P_f,0 + i P_f,1), unpacked to the
 // kx = 0..M half spectra Q4[f][kx][y].
 template <typename real, int N>
-__global__ __launch_bounds__(kGT) void k_gen_row_adj(const cplx<real>* __restrict__ G1, const real* __restrict__ U,
-                                                     const real* __restrict__ V, const real* __restrict__ Ox,
-                                                     const real* __restrict__ Oy, cplx<real>* __restrict__ Q4,
-                                                     const cplx<real>* __restrict__ twg) {
+__device__ inline void gen_row_adj(int y0, const cplx<real>* __restrict__ G1, const real* __restrict__ U,
+                                   const real* __restrict__ V, const real* __restrict__ Ox,
+                                   const real* __restrict__ Oy, cplx<real>* __restrict__ Q4,
+                                   const cplx<real>* __restrict__ twg) {
     using C = cplx<real>;
     using G = Geo2<N>;
     constexpr int M = G::M, MC = G::MC;
@@ -459,7 +482,6 @@ __global__ __launch_bounds__(kGT) void k_gen_row_adj(const cplx<real>* __restric
     __shared__ C sT[N];
     __shared__ C sA[4][N], sB[4][N];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int y0 = 2 * xcd_row_group(blockIdx.x, gridDim.x);
     // base fields of the thread's points of both rows, loaded first
     real bf[RX][4][2];
 #pragma unroll
@@ -520,14 +542,107 @@ __global__ __launch_bounds__(kGT) void k_gen_row_adj(const cplx<real>* __restric
     }
 }
 
+template <typename real, int N>
+__global__ __launch_bounds__(kGT) void k_gen_row_adj(const cplx<real>* __restrict__ G1, const real* __restrict__ U,
+                                                     const real* __restrict__ V, const real* __restrict__ Ox,
+                                                     const real* __restrict__ Oy, cplx<real>* __restrict__ Q4,
+                                                     const cplx<real>* __restrict__ twg) {
+    gen_row_adj<real, N>(2 * xcd_row_group(blockIdx.x, gridDim.x), G1, U, V, Ox, Oy, Q4, twg);
+}
+
+// ---- one launch per integration (genflow.hpp) ----------------------------------------
+enum FlowKind { FLOW_LIN = 0, FLOW_NL = 1, FLOW_ADJ = 2 };
+
+// Does nothing unless the launch before it gave up waiting: then one workgroup runs the
+// same integration stage by stage, and the words go back to tag 0.
+template <typename real, int N, int KIND>
+__global__ __launch_bounds__(kGT) void k_flow_repair(FlowArgs<real> g, real* W, real* Acc, cplx<real>* Q,
+                                                     cplx<real>* Gf, size_t words) {
+    if (__hip_atomic_load(g.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+    constexpr int MC = Geo2<N>::MC;
+    for (int n = -1; n < 4 * g.nsteps; ++n) {
+        const int q = n & 3, mode = n < 0 ? GEN_FIRST : n == 4 * g.nsteps - 1 ? GEN_LAST : GEN_STAGE;
+        for (int y0 = 0; n >= 0 && y0 < N; y0 += 2) {
+            if constexpr (KIND == FLOW_ADJ)
+                gen_row_adj<real, N>(y0, Q, g.U, g.V, g.Ox, g.Oy, Gf, g.tw);
+            else
+                gen_row<real, N, KIND == FLOW_NL ? ROW_NL : ROW_LIN, 2>(y0, Gf, g.U, g.V, g.Ox, g.Oy, Q, g.tw, g.U0);
+            __syncthreads();
+        }
+        for (int kx = 0; kx < MC; ++kx) {
+            if constexpr (KIND == FLOW_ADJ)
+                gen_col_adj<real, N>(kx, g.x, W, Acc, Gf, Q, g.y, g.tw, g.alpha, g.Re, g.dt, q, mode);
+            else
+                gen_col<real, N>(kx, g.x, W, Acc, Q, Gf, g.y, g.tw, g.alpha, g.Re, g.dt, q, mode, g.fvec);
+            __syncthreads();
+        }
+    }
+    for (size_t i = threadIdx.x; i < words; i += kGT) g.toRows[i] = 0;  // toCols follows toRows
+    __syncthreads();
+    if (threadIdx.x == 0) *g.failed = 0;
+}
+
+// The exchange of one Gen2D: words of both directions, the failure flag, the state
+// between launches, and the tag of the next stage.
+struct FlowWork {
+    DevBuf words, mid;
+    unsigned tag = 1;
+    int polls = kFlowPolls;
+    static size_t count(int N, bool fp32) { return size_t(5) * (fp32 ? 2 : 4) * ((N - 1) / 3 + 1) * N; }
+    tsk_status init(int N, bool fp32, size_t state_bytes) {
+        const size_t b = (count(N, fp32) + 1) * sizeof(unsigned long long);
+        TSK_TRY(words.ensure(b));
+        TSK_TRY(mid.ensure(state_bytes));
+        TSK_HIP(hipMemset(words.ptr, 0, b));
+        TSK_HIP(hipStreamSynchronize(nullptr));
+        return TSK_OK;
+    }
+};
+
+template <typename real, int N, int KIND>
+void flow_run(FlowWork& w, FlowArgs<real> g, real* W, real* Acc, cplx<real>* Q, cplx<real>* Gf, const void* x,
+              void* y, int nsteps, hipStream_t s) {
+    using G = FlowGeo<real, N>;
+    auto* base = w.words.as<unsigned long long>();
+    const size_t total = G::words(5);
+    g.toRows = base;
+    g.toCols = base + G::words(KIND == FLOW_ADJ ? 1 : 4);
+    g.failed = reinterpret_cast<unsigned*>(base + total);
+    g.polls = w.polls;
+    const int launches = (nsteps + kFlowSteps - 1) / kFlowSteps;
+    const void* in = x;
+    for (int c = 0; c < launches; ++c) {
+        void* out = (launches - 1 - c) % 2 == 0 ? y : w.mid.ptr;
+        g.x = static_cast<const real*>(in);
+        g.y = static_cast<real*>(out);
+        g.nsteps = std::min(kFlowSteps, nsteps - c * kFlowSteps);
+        g.tag = w.tag;
+        w.tag += 4u * unsigned(g.nsteps);
+        if constexpr (KIND == FLOW_ADJ)
+            hipLaunchKernelGGL((k_flow_adj<real, N>), dim3(G::blocks), dim3(kGT), 0, s, g);
+        else
+            hipLaunchKernelGGL((k_flow<real, N, KIND == FLOW_NL>), dim3(G::blocks), dim3(kGT), 0, s, g);
+        hipLaunchKernelGGL((k_flow_repair<real, N, KIND>), dim3(1), dim3(kGT), 0, s, g, W, Acc, Q, Gf, total);
+        in = out;
+    }
+}
+
 // nsteps transposed Lawson steps from x into y (G1 in the Q buffer, Q4 in G).
 template <typename real, int N>
-void gen_run_adj(const void* x, void* y, real* W, real* Acc, cplx<real>* G1, cplx<real>* Q4, const real* U,
-                 const real* V, const real* Ox, const real* Oy, const void* tw, double alpha, double Re, double dt,
-                 int nsteps, hipStream_t s) {
+void gen_run_adj(FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<real>* G1, cplx<real>* Q4, real* U,
+                 real* V, real* Ox, real* Oy, const void* tw, double alpha, double Re, double dt, int nsteps,
+                 hipStream_t s) {
     using C = cplx<real>;
     constexpr int MC = Geo2<N>::MC;
     const C* twc = static_cast<const C*>(tw);
+    if constexpr (flow_fits(N)) {
+        FlowArgs<real> g{};
+        g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
+        g.tw = twc;
+        g.alpha = alpha, g.Re = Re, g.dt = dt;
+        flow_run<real, N, FLOW_ADJ>(fw, g, W, Acc, G1, Q4, x, y, nsteps, s);
+        return;
+    }
     hipLaunchKernelGGL((k_gen_col_adj<real, N>), dim3(MC), dim3(kGT), 0, s, static_cast<const real*>(x), W, Acc, Q4,
                        G1, static_cast<real*>(y), twc, alpha, Re, dt, 0, int(GEN_FIRST));
     for (int st = 0; st < nsteps; ++st)
@@ -540,13 +655,13 @@ void gen_run_adj(const void* x, void* y, real* W, real* Acc, cplx<real>* G1, cpl
 }
 
 template <typename real>
-void gen_dispatch_adj(int N, const void* x, void* y, real* W, real* Acc, cplx<real>* G1, cplx<real>* Q4,
-                      const real* U, const real* V, const real* Ox, const real* Oy, const void* tw, double alpha,
-                      double Re, double dt, int nsteps, hipStream_t s) {
+void gen_dispatch_adj(int N, FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<real>* G1,
+                      cplx<real>* Q4, real* U, real* V, real* Ox, real* Oy, const void* tw, double alpha, double Re,
+                      double dt, int nsteps, hipStream_t s) {
     switch (N) {
 #define X(n)                                                                                                      \
     case n:                                                                                                       \
-        gen_run_adj<real, n>(x, y, W, Acc, G1, Q4, U, V, Ox, Oy, tw, alpha, Re, dt, nsteps, s);                   \
+        gen_run_adj<real, n>(fw, x, y, W, Acc, G1, Q4, U, V, Ox, Oy, tw, alpha, Re, dt, nsteps, s);               \
         break;
         X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
 #undef X
@@ -557,13 +672,22 @@ void gen_dispatch_adj(int N, const void* x, void* y, real* W, real* Acc, cplx<re
 // linearized / nonlinear (forcing fvec, drift U0) equation from x into y.
 // ROW_FIELDS: the grid fields of x into U, V, Ox, Oy (nsteps ignored).
 template <typename real, int N, int RM>
-void gen_run(const void* x, void* y, real* W, real* Acc, cplx<real>* Q, cplx<real>* Gf, real* U, real* V, real* Ox,
-             real* Oy, const void* tw, double alpha, double Re, double dt, int nsteps, double U0, const real* fvec,
-             hipStream_t s) {
+void gen_run(FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<real>* Q, cplx<real>* Gf, real* U,
+             real* V, real* Ox, real* Oy, const void* tw, double alpha, double Re, double dt, int nsteps, double U0,
+             const real* fvec, hipStream_t s) {
     using C = cplx<real>;
     constexpr int MC = Geo2<N>::MC;
     constexpr int RPW = gen_rows_per_group<real, N>();
     const C* twc = static_cast<const C*>(tw);
+    if constexpr (flow_fits(N) && RM != ROW_FIELDS) {
+        FlowArgs<real> g{};
+        g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
+        g.fvec = fvec;
+        g.tw = twc;
+        g.alpha = alpha, g.Re = Re, g.dt = dt, g.U0 = U0;
+        flow_run<real, N, RM == ROW_NL ? FLOW_NL : FLOW_LIN>(fw, g, W, Acc, Q, Gf, x, y, nsteps, s);
+        return;
+    }
     hipLaunchKernelGGL((k_gen_col<real, N>), dim3(MC), dim3(kGT), 0, s, static_cast<const real*>(x), W, Acc, Q, Gf,
                        static_cast<real*>(y), twc, alpha, Re, dt, 0, int(GEN_FIRST), fvec);
     if constexpr (RM == ROW_FIELDS) {
@@ -582,13 +706,13 @@ void gen_run(const void* x, void* y, real* W, real* Acc, cplx<real>* Q, cplx<rea
 }
 
 template <typename real, int RM>
-void gen_dispatch(int N, const void* x, void* y, real* W, real* Acc, cplx<real>* Q, cplx<real>* Gf, real* U, real* V,
-                  real* Ox, real* Oy, const void* tw, double alpha, double Re, double dt, int nsteps, double U0,
-                  const real* fvec, hipStream_t s) {
+void gen_dispatch(int N, FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<real>* Q, cplx<real>* Gf,
+                  real* U, real* V, real* Ox, real* Oy, const void* tw, double alpha, double Re, double dt, int nsteps,
+                  double U0, const real* fvec, hipStream_t s) {
     switch (N) {
 #define X(n)                                                                                                      \
     case n:                                                                                                       \
-        gen_run<real, n, RM>(x, y, W, Acc, Q, Gf, U, V, Ox, Oy, tw, alpha, Re, dt, nsteps, U0, fvec, s);          \
+        gen_run<real, n, RM>(fw, x, y, W, Acc, Q, Gf, U, V, Ox, Oy, tw, alpha, Re, dt, nsteps, U0, fvec, s);      \
         break;
         X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
 #undef X
@@ -601,6 +725,7 @@ struct Gen2D {
     int N = 0, M = 0;
     bool fp32 = false;
     DevBuf U, V, Ox, Oy, W, Acc, Q, G;
+    FlowWork flow;
 };
 
 tsk_status gen2d_create(int N, bool fp32, const double* U, const double* V, const double* Ox, const double* Oy,
@@ -627,22 +752,25 @@ tsk_status gen2d_create(int N, bool fp32, const double* U, const double* V, cons
     TSK_TRY(g->Acc.ensure(size_t(n) * rb));
     TSK_TRY(g->Q.ensure(size_t(g->M + 1) * N * 2 * rb));
     TSK_TRY(g->G.ensure(4 * size_t(g->M + 1) * N * 2 * rb));
+    if (flow_fits(N)) TSK_TRY(g->flow.init(N, fp32, size_t(n) * rb));
     *out = g.release();
     return TSK_OK;
 }
 
 void gen2d_free(Gen2D* g) { delete g; }
 
+void gen2d_set_polls(Gen2D* g, int polls) { g->flow.polls = polls < 0 ? kFlowPolls : polls; }
+
 namespace {
 template <int RM>
 tsk_status gen_go(Gen2D* g, double alpha, double Re, double dt, int nsteps, double U0, const void* fvec, const void* x,
                   void* y, const void* tw, hipStream_t s) {
     if (g->fp32)
-        gen_dispatch<float, RM>(g->N, x, y, g->W.as<float>(), g->Acc.as<float>(), g->Q.as<float2>(),
+        gen_dispatch<float, RM>(g->N, g->flow, x, y, g->W.as<float>(), g->Acc.as<float>(), g->Q.as<float2>(),
                                 g->G.as<float2>(), g->U.as<float>(), g->V.as<float>(), g->Ox.as<float>(),
                                 g->Oy.as<float>(), tw, alpha, Re, dt, nsteps, U0, static_cast<const float*>(fvec), s);
     else
-        gen_dispatch<double, RM>(g->N, x, y, g->W.as<double>(), g->Acc.as<double>(), g->Q.as<double2>(),
+        gen_dispatch<double, RM>(g->N, g->flow, x, y, g->W.as<double>(), g->Acc.as<double>(), g->Q.as<double2>(),
                                  g->G.as<double2>(), g->U.as<double>(), g->V.as<double>(), g->Ox.as<double>(),
                                  g->Oy.as<double>(), tw, alpha, Re, dt, nsteps, U0, static_cast<const double*>(fvec),
                                  s);
@@ -659,11 +787,11 @@ tsk_status gen2d_apply(Gen2D* g, double alpha, double Re, double dt, int nsteps,
 tsk_status gen2d_apply_adjoint(Gen2D* g, double alpha, double Re, double dt, int nsteps, const void* x, void* y,
                                const void* tw, hipStream_t s) {
     if (g->fp32)
-        gen_dispatch_adj<float>(g->N, x, y, g->W.as<float>(), g->Acc.as<float>(), g->Q.as<float2>(),
+        gen_dispatch_adj<float>(g->N, g->flow, x, y, g->W.as<float>(), g->Acc.as<float>(), g->Q.as<float2>(),
                                 g->G.as<float2>(), g->U.as<float>(), g->V.as<float>(), g->Ox.as<float>(),
                                 g->Oy.as<float>(), tw, alpha, Re, dt, nsteps, s);
     else
-        gen_dispatch_adj<double>(g->N, x, y, g->W.as<double>(), g->Acc.as<double>(), g->Q.as<double2>(),
+        gen_dispatch_adj<double>(g->N, g->flow, x, y, g->W.as<double>(), g->Acc.as<double>(), g->Q.as<double2>(),
                                  g->G.as<double2>(), g->U.as<double>(), g->V.as<double>(), g->Ox.as<double>(),
                                  g->Oy.as<double>(), tw, alpha, Re, dt, nsteps, s);
     TSK_HIP(hipGetLastError());
