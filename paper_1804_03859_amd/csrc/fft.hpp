@@ -156,35 +156,86 @@ __device__ inline C* fft_lds(C* a, C* b, const C* tw, int tid) {
     return fft_passes<N, 0, 1, SIGN, NT>(a, b, tw, tid);
 }
 
-// The transform by one wavefront alone: passes ordered by the wavefront itself, no
-// workgroup barrier (LDS operations of one wavefront complete in order).  Radix 4
-// before 8: one wavefront's time is the length of its longest lane, and a radix-8
-// pass of 128 points keeps 16 lanes busy with twice the work of radix 4 on 32.
-constexpr int fft_wave_radix(int N, int pass) {
-    int p = 0;
-    while (N % 4 == 0) { if (p == pass) return 4; N /= 4; ++p; }
-    if (N % 2 == 0) { if (p == pass) return 2; N /= 2; ++p; }
-    while (N % 3 == 0) { if (p == pass) return 3; N /= 3; ++p; }
-    return 1;
+// ---- the transform by one wavefront in registers ----------------------------------
+// N = R L, L = 2^p lanes (lanes beyond repeat them), R values each.  With lane l and
+// register r, b(l) the bit reversal of l:
+//     dif: in n = l + L r,    out k = r + R b(l)
+//     dit: in n = r + R b(l), out k = l + L r
+// R-point DFTs inside the lane, twiddles, and p radix-2 steps between lanes l and l ^ H
+// (DPP and permlane moves, no LDS).  A Stockham pass of one wavefront through LDS takes
+// some 450 cycles whatever its radix, a step here about 110; the constants stay in
+// registers.
+constexpr int lane_fft_lanes(int N) {
+    int l = 1;
+    while (l < kWave && N % (2 * l) == 0) l *= 2;
+    return l;
 }
-constexpr int fft_wave_num_passes(int N) {
-    int p = 0;
-    while (fft_wave_radix(N, p) > 1) ++p;
-    return p;
-}
-template <int N, int P, int NS, int SIGN, typename C>
-__device__ inline C* fft_wave_passes(C* a, C* b, const C* tw, int lane) {
-    if constexpr (P >= fft_wave_num_passes(N)) {
-        return a;
-    } else {
-        constexpr int R = fft_wave_radix(N, P);
-        fft_pass<N, R, NS, SIGN, kWave>(a, b, tw, lane);
-        wave_lds_sync();
-        return fft_wave_passes<N, P + 1, NS * R, SIGN>(b, a, tw, lane);
+template <typename real, int N> struct LaneFft {
+    using C = cplx<real>;
+    static constexpr int L = lane_fft_lanes(N), R = N / L;
+    static constexpr int P = L == 64 ? 6 : L == 32 ? 5 : L == 16 ? 4 : 0;
+    static_assert(P > 0 && R <= 4, "lanes and registers of a transform");
+    C w[P];   // step H = 2^p: W_{2H}^{l mod H} on lanes with bit H, else 1
+    real s[P];  // -1 on lanes with bit H, else 1
+    C u[R];   // W_N^{l r}
+    int l, rev;
+
+    __device__ void init(const C* __restrict__ tw) {
+        l = lane_id() & (L - 1);
+        rev = int(__brev(unsigned(l)) >> (32 - P));
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int H = 1 << p;
+            const bool up = (l & H) != 0;
+            w[p] = up ? tw[(l & (H - 1)) * (N / (2 * H))] : cmk<C>(real(1), real(0));
+            s[p] = up ? real(-1) : real(1);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r] = tw[l * r];
     }
-}
-template <int N, int SIGN, typename C> __device__ inline C* fft_wave(C* a, C* b, const C* tw, int lane) {
-    return fft_wave_passes<N, 0, 1, SIGN>(a, b, tw, lane);
-}
+    template <int SIGN> static __device__ C turn(C v, C z) {  // v z (forward) or v conj(z)
+        if constexpr (SIGN > 0) z.y = -z.y;
+        return cmul(v, z);
+    }
+    template <int SIGN> __device__ void in_lane(C (&v)[R]) const {
+        if constexpr (R > 1) dft<R, SIGN>(v);
+    }
+    template <int SIGN> __device__ void twiddle(C (&v)[R]) const {
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[r] = turn<SIGN>(v[r], u[r]);
+    }
+    template <int SIGN, int p> __device__ void dif_steps(C (&v)[R]) const {
+        constexpr int H = 1 << p;
+        const int lane = lane_id();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const C o = cmk<C>(xor_lane<H>(v[r].x, lane), xor_lane<H>(v[r].y, lane));
+            v[r] = cmk<C>(fma(s[p], v[r].x, o.x), fma(s[p], v[r].y, o.y));
+            if constexpr (p > 0) v[r] = turn<SIGN>(v[r], w[p]);
+        }
+        if constexpr (p > 0) dif_steps<SIGN, p - 1>(v);
+    }
+    template <int SIGN, int p> __device__ void dit_steps(C (&v)[R]) const {
+        constexpr int H = 1 << p;
+        const int lane = lane_id();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (p > 0) v[r] = turn<SIGN>(v[r], w[p]);
+            const C o = cmk<C>(xor_lane<H>(v[r].x, lane), xor_lane<H>(v[r].y, lane));
+            v[r] = cmk<C>(fma(s[p], v[r].x, o.x), fma(s[p], v[r].y, o.y));
+        }
+        if constexpr (p + 1 < P) dit_steps<SIGN, p + 1>(v);
+    }
+    template <int SIGN> __device__ void dif(C (&v)[R]) const {
+        in_lane<SIGN>(v);
+        twiddle<SIGN>(v);
+        dif_steps<SIGN, P - 1>(v);
+    }
+    template <int SIGN> __device__ void dit(C (&v)[R]) const {
+        dit_steps<SIGN, 0>(v);
+        twiddle<SIGN>(v);
+        in_lane<SIGN>(v);
+    }
+};
 
 }  // namespace tsk

@@ -5,10 +5,11 @@
 // loads the twiddles, the state and the base fields again and evaluates its
 // exponentials.  Here the MC column workgroups and N / 2 row workgroups each keep
 // theirs in registers and LDS for all stages; a stage is two hops between them.
-// Measured, us per hop (launches / this): FP64 16^2 4.2 / 2.0, 96^2 4.6 / 3.1, 128^2 5.4 /
-// 3.6; FP32 256^2 5.5 / 3.4.  A hop is about 1.4 us of memory latency, two transforms by
-// one wavefront (0.2 us at 16 points, 0.9 at 128 in FP64) and, from 192^2 in FP64 on,
-// the bandwidth of the scattered stores.
+// Measured, us per hop (launches / this): FP64 16^2 4.0 / 1.4, 96^2 4.8 / 2.9, 128^2 5.3 /
+// 3.1, 256^2 6.5 / 5.3; FP32 16^2 3.8 / 1.2, 256^2 5.5 / 3.4.  A hop is about 1 us of memory latency, two
+// transforms by one wavefront (fft.hpp's register form; through LDS with workgroup
+// barriers a hop took 2.1, 3.9, 4.2, 7.1 and 4.2) and, from 192^2 in FP64 on, the traffic
+// of the words.
 //
 // Exchange.  A hop carries 32-bit halves of the values in 64-bit words (tag << 32 |
 // bits), written and read whole by relaxed device-scope atomics, the tag numbering
@@ -25,11 +26,13 @@
 // the launch drains; k_flow_repair, launched behind it, computes the integration by
 // one workgroup with plain memory if it finds `failed` set, and clears the words.
 //
-// A complex value is a cell of 4 (FP64) or 2 (FP32) words, moved by 16-byte accesses
-// (the words of an access need not arrive together).  Layouts (p: row pair, r: row of it):
-//     columns -> rows   [p][field][kx][r]   a row wavefront reads runs of kx
-//     rows -> columns   [kx][field][y]      a column wavefront reads runs of y
-// so that readers, which poll, touch whole lines, and writers 64 (FP32 32) bytes at once.
+// A complex value is a cell of 4 (FP64) or 2 (FP32) words, moved as one or two quads of
+// 16 bytes (the words of an access need not arrive together).  Layouts (p: row pair,
+// r: row of it, q: quad):
+//     columns -> rows   [p][field][kx][q][r]   a row wavefront reads runs of kx
+//     rows -> columns   [kx][field][p][q][r]   a column wavefront reads runs of y
+// so that readers, which poll, touch whole lines, and adjacent lanes of a writer 32 bytes
+// at once.
 #pragma once
 
 #include "fft.hpp"
@@ -81,6 +84,10 @@ __device__ inline float2 flow_value(const quad (&d)[1]) {
     return make_float2(__uint_as_float(d[0].x), __uint_as_float(d[0].z));
 }
 
+// Byte offset of quad i of a cell (cells 2 c and 2 c + 1 are a pair of rows).
+template <int Q> __device__ inline int flow_at(unsigned cell, int i) {
+    return int((cell >> 1) * (32 * Q) + (cell & 1) * 16 + 32 * i);
+}
 template <typename C, typename real = decltype(C{}.x)>
 __device__ inline void flow_send(FlowBuf buf, unsigned cell, C v, unsigned tag) {
     constexpr int Q = kFlowQuads<real>;
@@ -88,13 +95,15 @@ __device__ inline void flow_send(FlowBuf buf, unsigned cell, C v, unsigned tag) 
     flow_pack(v, tag, d);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        __builtin_amdgcn_raw_buffer_store_b128(d[i], buf, int(cell * (16 * Q) + 16 * i), 0, kFlowScope);
+        __builtin_amdgcn_raw_buffer_store_b128(d[i], buf, flow_at<Q>(cell, i), 0, kFlowScope);
 }
 
 // K cells per lane into v.  LIGHT: polls one access per lane until it has arrived and
 // reads the rest then; else polls everything.  One trip more after the arrival against
-// polls that crowd the stores they wait for: us per hop all / light, FP64 96^2 3.28 /
-// 3.37, 128^2 4.17 / 4.00, 256^2 7.07 / 5.68; FP32 192^2 3.47 / 3.56, 256^2 4.21 / 3.80.
+// polls that crowd the stores they wait for: us per hop all / light, FP64 96^2 2.96 /
+// 3.02, 128^2 3.40 / 3.23, 256^2 6.86 / 5.42; FP32 192^2 2.84 / 2.91, 256^2 3.98 / 3.63;
+// light for the four-field direction alone 128^2 3.07, 256^2 5.28, FP32 256^2 3.43.  Two
+// polls in flight are no faster.
 struct FlowWait {
     unsigned* failed;
     int polls;
@@ -116,7 +125,7 @@ __device__ inline void flow_recv(FlowBuf buf, const unsigned (&cell)[K], unsigne
             for (int k = 0; k < K; ++k)
 #pragma unroll
                 for (int i = 0; i < Q; ++i)
-                    d[k][i] = __builtin_amdgcn_raw_buffer_load_b128(buf, int(cell[k] * (16 * Q) + 16 * i), 0,
+                    d[k][i] = __builtin_amdgcn_raw_buffer_load_b128(buf, flow_at<Q>(cell[k], i), 0,
                                                                     kFlowScope | kFlowVolatile);
 #pragma unroll
             for (int k = 0; k < K; ++k)
@@ -124,7 +133,7 @@ __device__ inline void flow_recv(FlowBuf buf, const unsigned (&cell)[K], unsigne
                 for (int i = 0; i < Q; ++i) ok = ok && d[k][i].y == tag && d[k][i].w == tag;
             if (__all(ok)) break;
         } else {
-            const quad t = __builtin_amdgcn_raw_buffer_load_b128(buf, int(cell[K - 1] * (16 * Q) + 16 * (Q - 1)), 0,
+            const quad t = __builtin_amdgcn_raw_buffer_load_b128(buf, flow_at<Q>(cell[K - 1], Q - 1), 0,
                                                                  kFlowScope | kFlowVolatile);
             all = __all(t.y == tag);
         }
@@ -143,9 +152,8 @@ __device__ inline void flow_recv(FlowBuf buf, const unsigned (&cell)[K], unsigne
 // ---- geometry -----------------------------------------------------------------------
 template <typename real, int N> struct FlowGeo {
     static constexpr int M = (N - 1) / 3, MC = M + 1, NM = 2 * M + 1;
-    static constexpr int TI = (N + kWave - 1) / kWave;        // grid points of a column per lane
-    static constexpr int KI = (MC + kWave - 1) / kWave;       // kx per lane
-    static constexpr int SI = (2 * MC + kWave - 1) / kWave;   // (kx, row of the pair) per lane
+    static constexpr int KI = (MC + kWave - 1) / kWave;      // kx per lane
+    static constexpr int SI = (2 * MC + kWave - 1) / kWave;  // (kx, row of the pair) per lane
     static constexpr int blocks = MC + N / 2;
     static constexpr size_t words(int fields) { return size_t(fields) * 2 * kFlowQuads<real> * MC * N; }
     // Cells.
@@ -155,7 +163,8 @@ template <typename real, int N> struct FlowGeo {
     static __device__ inline unsigned col_at(int fields, int f, int kx, int y) {
         return unsigned((kx * fields + f) * N + y);
     }
-    static constexpr bool light = N * sizeof(real) >= 1024;
+    // flow_recv's light polls: readers of four fields, from 1 KB a transform on.
+    static constexpr bool light(int fields) { return fields == 4 && N * sizeof(real) >= 1024; }
 };
 
 // Grids that run this way: one mode per thread, and workgroups small enough that the
@@ -163,10 +172,10 @@ template <typename real, int N> struct FlowGeo {
 constexpr bool flow_fits(int N) { return N <= 256; }
 constexpr int kFlowSteps = 512;  // steps per launch (a few ms)
 
-// FP64 at N = 256: 39 KB, four workgroups per CU, so that four launches (one per
-// hardware queue of a process) are resident together.
+// FP64 at N = 256: 35 KB and at most 128 registers, four workgroups per CU, so that four
+// launches (one per hardware queue of a process) are resident together.
 template <typename real, int N> struct FlowLds {
-    cplx<real> A[4][N], B[4][N], T[N], S[FlowGeo<real, N>::NM];
+    cplx<real> A[4][N], B[4][N], S[FlowGeo<real, N>::NM];
 };
 
 // A packed mode of a column by its grid index t, or none: entry of the segment,
@@ -176,17 +185,17 @@ template <int M> __device__ inline bool flow_mode(int t, int N, int kx, int& e, 
     conj = kx == 0 && jy < 0;
     if (conj) jy = -jy;
     e = kx == 0 ? jy - 1 : jy + M;
-    return t < N && jy <= M && jy >= -M && (kx > 0 || jy > 0);
+    return jy <= M && jy >= -M && (kx > 0 || jy > 0);
 }
 
 // The pair's half spectra (kx = 0 .. M of rows 0 and 1 at src) received into the spectrum
-// of row 0 + i row 1.
-template <typename real, int N, int K, typename C = cplx<real>>
+// of row 0 + i row 1 (its modes beyond M stay zero).
+template <typename real, int N, int F, int K, typename C = cplx<real>>
 __device__ inline void flow_unpair(FlowBuf rows, const unsigned (&src)[K], unsigned tag, FlowWait& wt, C* a,
                                    int lane) {
     using G = FlowGeo<real, N>;
     C v[K];
-    flow_recv<G::light>(rows, src, tag, v, wt);
+    flow_recv<G::light(F)>(rows, src, tag, v, wt);
 #pragma unroll
     for (int i = 0; i < K / 2; ++i) {
         const int k = lane + kWave * i;
@@ -199,22 +208,43 @@ __device__ inline void flow_unpair(FlowBuf rows, const unsigned (&src)[K], unsig
         a[k] = cmk<C>(g0.x - g1.y, g0.y + g1.x);
         if (k > 0) a[N - k] = cmk<C>(g0.x + g1.y, g1.x - g0.y);
     }
-    for (int t = G::MC + lane; t < N - G::M; t += kWave) a[t] = cmk<C>(real(0), real(0));
+    wave_lds_sync();
 }
-// Half spectrum k of row r from the spectrum of row 0 + i row 1.
-template <int N, typename C> __device__ inline C flow_split(const C* Z, int k, int r) {
-    using real = decltype(C{}.x);
-    const C za = Z[k], zb = cconj(Z[k == 0 ? 0 : N - k]);
-    return r == 0 ? cmk<C>(real(0.5) * (za.x + zb.x), real(0.5) * (za.y + zb.y))
-                  : cmk<C>(real(0.5) * (za.y - zb.y), real(-0.5) * (za.x - zb.x));
+// The spectrum of row 0 + i row 1 (k = l + L r, through Z) split into the pair's half
+// spectra and sent as field f.
+template <typename real, int N, typename C = cplx<real>>
+__device__ inline void flow_split(FlowBuf cols, const LaneFft<real, N>& ft, const C (&v)[LaneFft<real, N>::R], C* Z,
+                                  int fields, int f, int y0, unsigned tag, int lane) {
+    using G = FlowGeo<real, N>;
+    using T = LaneFft<real, N>;
+#pragma unroll
+    for (int r = 0; r < T::R; ++r)
+        if (lane < T::L) Z[lane + T::L * r] = v[r];
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < G::SI; ++i) {
+        const int k = (lane + kWave * i) >> 1;
+        if (k > G::M) continue;
+        const C za = Z[k], zb = cconj(Z[k == 0 ? 0 : N - k]);
+        const C h = (lane & 1) == 0 ? cmk<C>(real(0.5) * (za.x + zb.x), real(0.5) * (za.y + zb.y))
+                                    : cmk<C>(real(0.5) * (za.y - zb.y), real(-0.5) * (za.x - zb.x));
+        flow_send(cols, G::col_at(fields, f, k, y0 + (lane & 1)), h, tag);
+    }
+    wave_lds_sync();
 }
+
+// The barriers below: column workgroups put their stage input into S (barrier), its
+// transforms go out; the answer's transform goes to A (barrier).  A row workgroup's
+// wavefronts put their transforms into B (one barrier); they write B again only on
+// words that the columns send after all of this workgroup's.
 
 // ---- forward: linearized (ROW_LIN) and nonlinear (ROW_NL) ----------------------------
 template <typename real, int N>
 __device__ void flow_col(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
     using C = cplx<real>;
     using G = FlowGeo<real, N>;
-    constexpr int M = G::M, MC = G::MC, NM = G::NM, TI = G::TI;
+    using T = LaneFft<real, N>;
+    constexpr int M = G::M, NM = G::NM, R = T::R, L = T::L;
     const int tid = int(threadIdx.x), lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int nq = kx == 0 ? M : NM;
@@ -222,6 +252,8 @@ __device__ void flow_col(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
     const double kxv = g.alpha * kx;
     FlowWait wt{g.failed, g.polls};
     const FlowBuf rows = flow_buf(g.toRows, G::words(4)), cols = flow_buf(g.toCols, G::words(1));
+    T ft;
+    ft.init(g.tw);
     // the thread's mode
     const bool act = tid < nq;
     const int my = kx == 0 ? tid + 1 : tid - M, ix = my < 0 ? my + N : my;
@@ -239,21 +271,21 @@ __device__ void flow_col(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
         }
         s.S[tid] = cmk<C>(wx, wy);
     }
-    // wavefront f: factors of derived field f at the lane's points t = lane + 64 i
-    int en[TI];
-    unsigned keep = 0;
-    double cr[TI], ci[TI];
+    // wavefront f: factors of derived field f (i c s; c = kx, ky, ky/K^2, -kx/K^2) at the
+    // lane's points of the inverse transform
+    int en[R];
+    unsigned keep = 0, conjs = 0;
+    double cf[R];
 #pragma unroll
-    for (int i = 0; i < TI; ++i) {
+    for (int r = 0; r < R; ++r) {
         int e, jy;
         bool conj;
-        const bool kept = flow_mode<M>(lane + kWave * i, N, kx, e, conj, jy);
+        const bool kept = flow_mode<M>(r + R * ft.rev, N, kx, e, conj, jy);
         const double K2 = kept ? kxv * kxv + double(jy) * jy : 1.0;
-        const double c = wv == 0 ? kxv : wv == 1 ? double(jy) : wv == 2 ? double(jy) / K2 : -kxv / K2;
-        keep |= unsigned(kept) << i;
-        en[i] = kept ? e : 0;
-        cr[i] = -c;
-        ci[i] = conj ? -c : c;
+        cf[r] = wv == 0 ? kxv : wv == 1 ? double(jy) : wv == 2 ? double(jy) / K2 : -kxv / K2;
+        en[r] = kept ? e : 0;
+        keep |= unsigned(kept) << r;
+        conjs |= unsigned(conj) << r;
     }
     const double h = g.dt, h2 = 0.5 * g.dt, h3 = g.dt / 3.0, h6 = g.dt / 6.0;
     const double scl = -1.0 / (double(N) * N);
@@ -261,39 +293,31 @@ __device__ void flow_col(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
     for (int st = 0; st < g.nsteps; ++st)
         for (int q = 0; q < 4; ++q, ++tag) {
             __syncthreads();
-            C* a = s.A[wv];
+            C v[R];
 #pragma unroll
-            for (int i = 0; i < TI; ++i) {
-                const int t = lane + kWave * i;
-                const C sv = s.S[en[i]];
-                const C d = cmk<C>(real(cr[i] * double(sv.y)), real(ci[i] * double(sv.x)));
-                if (t < N) a[t] = (keep >> i & 1) ? d : cmk<C>(real(0), real(0));
+            for (int r = 0; r < R; ++r) {
+                const C sv = s.S[en[r]];
+                const real dx = real(-cf[r] * double(sv.y)), dy = real(cf[r] * double(sv.x));
+                const bool kept = keep >> r & 1;
+                v[r] = cmk<C>(kept ? dx : real(0), kept ? ((conjs >> r & 1) ? -dy : dy) : real(0));
             }
-            wave_lds_sync();
-            const C* X = fft_wave<N, +1>(a, s.B[wv], s.T, lane);
+            ft.template dit<+1>(v);
 #pragma unroll
-            for (int i = 0; i < TI; ++i) {
-                const int t = lane + kWave * i;
-                if (t < N) flow_send(rows, G::row_at(4, wv, t, kx), X[t], tag);
-            }
+            for (int r = 0; r < R; ++r)
+                if (lane < L) flow_send(rows, G::row_at(4, wv, lane + L * r, kx), v[r], tag);
             if (wv == 0) {
-                unsigned p[TI];
-                C v[TI];
+                unsigned p[R];
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int t = lane + kWave * i;
-                    p[i] = G::col_at(1, 0, kx, t < N ? t : lane % N);
-                }
-                flow_recv<G::light>(cols, p, tag, v, wt);
+                for (int r = 0; r < R; ++r) p[r] = G::col_at(1, 0, kx, ft.l + L * r);
+                flow_recv<G::light(1)>(cols, p, tag, v, wt);
+                ft.template dif<-1>(v);
 #pragma unroll
-                for (int i = 0; i < TI; ++i)
-                    if (lane + kWave * i < N) s.A[0][lane + kWave * i] = v[i];
-                wave_lds_sync();
-                fft_wave<N, -1>(s.A[0], s.B[0], s.T, lane);
+                for (int r = 0; r < R; ++r)
+                    if (lane < L) s.A[0][r + R * ft.rev] = v[r];
             }
             __syncthreads();
             if (act) {
-                const C xr = fft_wave_num_passes(N) % 2 == 0 ? s.A[0][ix] : s.B[0][ix];
+                const C xr = s.A[0][ix];
                 const double nx = scl * double(xr.x) + fx, ny = scl * double(xr.y) + fy;
                 double sx, sy;
                 if (q == 0) {
@@ -321,72 +345,77 @@ __device__ void flow_col(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
     }
 }
 
-// Wavefront f transforms field f of both rows of the pair, packed as row 0 + i row 1.
+// The base field that multiplies field f (wavefront f's, d_x w, d_y w, u, v) at the lane's
+// points x = r + R b(l) of both rows.
+template <typename real, int N, int R>
+__device__ inline void flow_base(const FlowArgs<real>& g, const LaneFft<real, N>& ft, int f, int y0, real (&b)[R][2]) {
+    const real* bf = f == 0 ? g.U : f == 1 ? g.V : f == 2 ? g.Ox : g.Oy;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) b[i][r] = bf[size_t(y0 + r) * N + i + R * ft.rev];
+}
+
+// Wavefront f transforms field f of both rows of the pair, packed as row 0 + i row 1 (and
+// multiplies it by its base field); the first forms the products, or adds them, and
+// transforms them back.
 template <typename real, int N, bool NL>
 __device__ void flow_row(const FlowArgs<real>& g, FlowLds<real, N>& s, int p) {
     using C = cplx<real>;
     using G = FlowGeo<real, N>;
-    constexpr int M = G::M, MC = G::MC, KI = G::KI, SI = G::SI;
+    using T = LaneFft<real, N>;
+    constexpr int M = G::M, MC = G::MC, KI = G::KI, R = T::R, L = T::L;
     const int tid = int(threadIdx.x), lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), y0 = 2 * p;
     FlowWait wt{g.failed, g.polls};
     const FlowBuf rows = flow_buf(g.toRows, G::words(4)), cols = flow_buf(g.toCols, G::words(1));
-    real bU[2], bV[2], bOx[2], bOy[2];
-    if constexpr (!NL) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const size_t o = size_t(y0 + r) * N + (tid < N ? tid : 0);
-            bU[r] = g.U[o];
-            bV[r] = g.V[o];
-            bOx[r] = g.Ox[o];
-            bOy[r] = g.Oy[o];
-        }
-    }
+    T ft;
+    ft.init(g.tw);
+    real b[R][2];
+    if constexpr (!NL) flow_base(g, ft, wv, y0, b);
     unsigned src[2 * KI];
 #pragma unroll
     for (int i = 0; i < 2 * KI; ++i) {
         const int k = lane + kWave * (i >> 1);
         src[i] = G::row_at(4, wv, y0 + (i & 1), k <= M ? k : M);
     }
+    for (int t = MC + lane; t < N - M; t += kWave) s.A[wv][t] = cmk<C>(real(0), real(0));
     unsigned tag = g.tag;
     for (int n = 0; n < 4 * g.nsteps; ++n, ++tag) {
-        flow_unpair<real, N>(rows, src, tag, wt, s.A[wv], lane);
-        wave_lds_sync();
-        fft_wave<N, +1>(s.A[wv], s.B[wv], s.T, lane);
-        __syncthreads();
-        C(*res)[N] = fft_wave_num_passes(N) % 2 == 0 ? s.A : s.B;
-        C(*fre)[N] = fft_wave_num_passes(N) % 2 == 0 ? s.B : s.A;
-        if (tid < N) {
-            const C wx = res[0][tid], wy = res[1][tid], u = res[2][tid], v = res[3][tid];
-            if constexpr (NL) {
-                const real is2 = real(0.70710678118654752440), u0 = real(g.U0);
-                fre[0][tid] = cmk<C>(is2 * (u.x * wx.x + v.x * wy.x) + u0 * wx.x,
-                                     is2 * (u.y * wx.y + v.y * wy.y) + u0 * wx.y);
-            } else {
-                fre[0][tid] = cmk<C>(bU[0] * wx.x + bV[0] * wy.x + bOx[0] * u.x + bOy[0] * v.x,
-                                     bU[1] * wx.y + bV[1] * wy.y + bOx[1] * u.y + bOy[1] * v.y);
-            }
-        }
-        __syncthreads();
-        if (wv == 0) {
-            // (the other wavefronts write their buffers again only on words that the
-            // columns send after the words below)
-            const C* Z = fft_wave<N, -1>(fre[0], fre[1], s.T, lane);
+        flow_unpair<real, N, 4>(rows, src, tag, wt, s.A[wv], lane);
+        C v[R];
 #pragma unroll
-            for (int i = 0; i < SI; ++i) {
-                const int k = (lane + kWave * i) >> 1;
-                if (k > M) continue;
-                flow_send(cols, G::col_at(1, 0, k, y0 + (lane & 1)), flow_split<N>(Z, k, lane & 1), tag);
+        for (int r = 0; r < R; ++r) v[r] = s.A[wv][ft.l + L * r];
+        ft.template dif<+1>(v);
+        if constexpr (!NL) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = cmk<C>(b[r][0] * v[r].x, b[r][1] * v[r].y);
+        }
+        if (wv > 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (lane < L) s.B[wv][lane + L * r] = v[r];
+        }
+        __syncthreads();
+        if (wv > 0) continue;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const C wx = v[r], wy = s.B[1][ft.l + L * r], u = s.B[2][ft.l + L * r], w = s.B[3][ft.l + L * r];
+            if constexpr (NL) {
+                const real is2 = real(0.70710678118654752440), u0 = real(g.U0);  // the packing factor sqrt(2) once
+                v[r] = cmk<C>(is2 * (u.x * wx.x + w.x * wy.x) + u0 * wx.x, is2 * (u.y * wx.y + w.y * wy.y) + u0 * wx.y);
+            } else {
+                v[r] = cmk<C>(((wx.x + wy.x) + u.x) + w.x, ((wx.y + wy.y) + u.y) + w.y);
             }
         }
+        ft.template dit<-1>(v);
+        flow_split<real, N>(cols, ft, v, s.B[0], 1, 0, y0, tag, lane);
     }
 }
 
 template <typename real, int N, bool NL>
-__global__ __launch_bounds__(4 * kWave) void k_flow(FlowArgs<real> g) {
+__global__ __launch_bounds__(4 * kWave, 4) void k_flow(FlowArgs<real> g) {
     __shared__ FlowLds<real, N> s;
-    for (int t = int(threadIdx.x); t < N; t += 4 * kWave) s.T[t] = g.tw[t];
-    __syncthreads();
     const int b = int(blockIdx.x);
     if (b < FlowGeo<real, N>::MC)
         flow_col<real, N>(g, s, b);
@@ -399,7 +428,8 @@ template <typename real, int N>
 __device__ void flow_col_adj(const FlowArgs<real>& g, FlowLds<real, N>& s, int kx) {
     using C = cplx<real>;
     using G = FlowGeo<real, N>;
-    constexpr int M = G::M, MC = G::MC, NM = G::NM, TI = G::TI;
+    using T = LaneFft<real, N>;
+    constexpr int M = G::M, NM = G::NM, R = T::R, L = T::L;
     const int tid = int(threadIdx.x), lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int nq = kx == 0 ? M : NM;
@@ -408,6 +438,9 @@ __device__ void flow_col_adj(const FlowArgs<real>& g, FlowLds<real, N>& s, int k
     const double h = g.dt, h2 = 0.5 * g.dt, h3 = g.dt / 3.0, h6 = g.dt / 6.0;
     const double scl = 1.0 / (double(N) * N);
     FlowWait wt{g.failed, g.polls};
+    const FlowBuf rows = flow_buf(g.toRows, G::words(1)), cols = flow_buf(g.toCols, G::words(4));
+    T ft;
+    ft.init(g.tw);
     const bool act = tid < nq;
     const int my = kx == 0 ? tid + 1 : tid - M, ix = my < 0 ? my + N : my;
     double e1 = 0.0, eh = 0.0, cf[4] = {0.0, 0.0, 0.0, 0.0};
@@ -424,50 +457,46 @@ __device__ void flow_col_adj(const FlowArgs<real>& g, FlowLds<real, N>& s, int k
         zy = g.x[o + 1];
         s.S[tid] = cmk<C>(real(h6 * double(zx)), real(h6 * double(zy)));
     }
-    const FlowBuf rows = flow_buf(g.toRows, G::words(1)), cols = flow_buf(g.toCols, G::words(4));
-    unsigned src[TI];
+    int en[R];
+    unsigned keep = 0, conjs = 0, src[R];
 #pragma unroll
-    for (int i = 0; i < TI; ++i) {
-        const int t = lane + kWave * i;
-        src[i] = G::col_at(4, wv, kx, t < N ? t : lane % N);
+    for (int r = 0; r < R; ++r) {
+        int e, jy;
+        bool conj;
+        const bool kept = flow_mode<M>(r + R * ft.rev, N, kx, e, conj, jy);
+        en[r] = kept ? e : 0;
+        keep |= unsigned(kept) << r;
+        conjs |= unsigned(conj) << r;
+        src[r] = G::col_at(4, wv, kx, ft.l + L * r);
     }
     unsigned tag = g.tag;
     for (int st = 0; st < g.nsteps; ++st)
         for (int q = 0; q < 4; ++q, ++tag) {
             __syncthreads();
+            C v[R];
             if (wv == 0) {
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int t = lane + kWave * i;
-                    int e, jy;
-                    bool conj;
-                    const bool kept = flow_mode<M>(t, N, kx, e, conj, jy);
-                    C v = s.S[kept ? e : 0];
-                    if (conj) v = cconj(v);
-                    if (t < N) s.A[0][t] = kept ? v : cmk<C>(real(0), real(0));
+                for (int r = 0; r < R; ++r) {
+                    const C sv = s.S[en[r]];
+                    const bool kept = keep >> r & 1;
+                    v[r] = cmk<C>(kept ? sv.x : real(0), kept ? ((conjs >> r & 1) ? -sv.y : sv.y) : real(0));
                 }
-                wave_lds_sync();
-                const C* X = fft_wave<N, +1>(s.A[0], s.B[0], s.T, lane);
+                ft.template dit<+1>(v);
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int t = lane + kWave * i;
-                    if (t < N) flow_send(rows, G::row_at(1, 0, t, kx), X[t], tag);
-                }
-                wave_lds_sync();
+                for (int r = 0; r < R; ++r)
+                    if (lane < L) flow_send(rows, G::row_at(1, 0, lane + L * r, kx), v[r], tag);
             }
-            C v[TI];
-            flow_recv<G::light>(cols, src, tag, v, wt);
+            flow_recv<G::light(4)>(cols, src, tag, v, wt);
+            ft.template dif<-1>(v);
 #pragma unroll
-            for (int i = 0; i < TI; ++i)
-                if (lane + kWave * i < N) s.A[wv][lane + kWave * i] = v[i];
-            wave_lds_sync();
-            fft_wave<N, -1>(s.A[wv], s.B[wv], s.T, lane);
+            for (int r = 0; r < R; ++r)
+                if (lane < L) s.A[wv][r + R * ft.rev] = v[r];
             __syncthreads();
             if (act) {
                 double sx = 0.0, sy = 0.0;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
-                    const C xf = fft_wave_num_passes(N) % 2 == 0 ? s.A[f][ix] : s.B[f][ix];
+                    const C xf = s.A[f][ix];
                     sx -= cf[f] * double(xf.y);
                     sy += cf[f] * double(xf.x);
                 }
@@ -499,58 +528,55 @@ __device__ void flow_col_adj(const FlowArgs<real>& g, FlowLds<real, N>& s, int k
     }
 }
 
+// The first wavefront transforms both rows (row 0 + i row 1); wavefront f multiplies by
+// base field f and transforms the products.
 template <typename real, int N>
 __device__ void flow_row_adj(const FlowArgs<real>& g, FlowLds<real, N>& s, int p) {
     using C = cplx<real>;
     using G = FlowGeo<real, N>;
-    constexpr int M = G::M, MC = G::MC, KI = G::KI, SI = G::SI;
+    using T = LaneFft<real, N>;
+    constexpr int M = G::M, MC = G::MC, KI = G::KI, R = T::R, L = T::L;
     const int tid = int(threadIdx.x), lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), y0 = 2 * p;
     FlowWait wt{g.failed, g.polls};
-    real bf[4][2];
-#pragma unroll
-    for (int rr = 0; rr < 2; ++rr) {
-        const size_t o = size_t(y0 + rr) * N + (tid < N ? tid : 0);
-        bf[0][rr] = g.U[o];
-        bf[1][rr] = g.V[o];
-        bf[2][rr] = g.Ox[o];
-        bf[3][rr] = g.Oy[o];
-    }
     const FlowBuf rows = flow_buf(g.toRows, G::words(1)), cols = flow_buf(g.toCols, G::words(4));
+    T ft;
+    ft.init(g.tw);
+    real b[R][2];
+    flow_base(g, ft, wv, y0, b);
     unsigned src[2 * KI];
 #pragma unroll
     for (int i = 0; i < 2 * KI; ++i) {
         const int k = lane + kWave * (i >> 1);
         src[i] = G::row_at(1, 0, y0 + (i & 1), k <= M ? k : M);
     }
+    for (int t = MC + tid; t < N - M; t += 4 * kWave) s.A[0][t] = cmk<C>(real(0), real(0));
+    __syncthreads();
     unsigned tag = g.tag;
     for (int n = 0; n < 4 * g.nsteps; ++n, ++tag) {
+        C v[R];
         if (wv == 0) {
-            flow_unpair<real, N>(rows, src, tag, wt, s.A[0], lane);
-            wave_lds_sync();
-            fft_wave<N, +1>(s.A[0], s.B[0], s.T, lane);
+            flow_unpair<real, N, 1>(rows, src, tag, wt, s.A[0], lane);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = s.A[0][ft.l + L * r];
+            ft.template dif<+1>(v);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (lane < L) s.B[0][lane + L * r] = v[r];
         }
         __syncthreads();
-        if (tid < N) {
-            const C v = fft_wave_num_passes(N) % 2 == 0 ? s.A[0][tid] : s.B[0][tid];
 #pragma unroll
-            for (int f = 0; f < 4; ++f) s.A[f][tid] = cmk<C>(bf[f][0] * v.x, bf[f][1] * v.y);
+        for (int r = 0; r < R; ++r) {
+            const C z = s.B[0][ft.l + L * r];
+            v[r] = cmk<C>(b[r][0] * z.x, b[r][1] * z.y);
         }
-        __syncthreads();
-        const C* Z = fft_wave<N, -1>(s.A[wv], s.B[wv], s.T, lane);
-#pragma unroll
-        for (int i = 0; i < SI; ++i) {
-            const int k = (lane + kWave * i) >> 1;
-            if (k > M) continue;
-            flow_send(cols, G::col_at(4, wv, k, y0 + (lane & 1)), flow_split<N>(Z, k, lane & 1), tag);
-        }
+        ft.template dit<-1>(v);
+        flow_split<real, N>(cols, ft, v, wv == 0 ? s.B[1] : s.A[wv], 4, wv, y0, tag, lane);
     }
 }
 
-template <typename real, int N> __global__ __launch_bounds__(4 * kWave) void k_flow_adj(FlowArgs<real> g) {
+template <typename real, int N> __global__ __launch_bounds__(4 * kWave, 4) void k_flow_adj(FlowArgs<real> g) {
     __shared__ FlowLds<real, N> s;
-    for (int t = int(threadIdx.x); t < N; t += 4 * kWave) s.T[t] = g.tw[t];
-    __syncthreads();
     const int b = int(blockIdx.x);
     if (b < FlowGeo<real, N>::MC)
         flow_col_adj<real, N>(g, s, b);
