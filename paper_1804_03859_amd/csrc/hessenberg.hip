@@ -37,6 +37,7 @@
 // converged one also count as copies of it (FP32 rounding splits a multiple
 // eigenvalue into a cluster of about that width), and a pair counts as
 // converged below max(tol, res_floor |mu|), the FP32 floor of the estimate.
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
@@ -114,26 +115,35 @@ __device__ inline double tri_eigvec(const double2* T, int p, int i, double2* zc)
 // ---- wanted set (shared by the complex and the real eigensolver) ----------------------
 // converged: res <= max(tol, res_floor |mu|); order by |mu| descending (ties:
 // larger arg first, then index); skip unresolved copies; first k accepted.
-__device__ inline void select_wanted(const double2* __restrict__ mu, const double* __restrict__ res,
+__device__ inline void select_wanted(const double2* __restrict__ mug, const double* __restrict__ resg,
                                      int* __restrict__ sel, RitzResult* __restrict__ rr, double* ctol, int* order,
                                      int* dupc, int p, int k, double tol, double dup_rel, double res_floor,
                                      int failed, int total, int lane) {
-    // converged: res <= max(tol, res_floor |mu|)
-    for (int i = lane; i < p; i += kHT) ctol[i] = fmax(tol, res_floor * cabs(mu[i]));
+    // the values, their moduli and arguments once, in LDS
+    __shared__ double2 mu[kMaxKrylov];
+    __shared__ double res[kMaxKrylov], mabs[kMaxKrylov], marg[kMaxKrylov];
+    for (int i = lane; i < p; i += kHT) {
+        const double2 m = mug[i];
+        mu[i] = m;
+        res[i] = resg[i];
+        mabs[i] = cabs(m);
+        marg[i] = atan2(m.y, m.x);
+        ctol[i] = fmax(tol, res_floor * mabs[i]);  // converged: res <= max(tol, res_floor |mu|)
+    }
     __syncthreads();
     for (int i = lane; i < p; i += kHT) {
-        double mi = cabs(mu[i]), ai = atan2(mu[i].y, mu[i].x);
+        const double mi = mabs[i], ai = marg[i];
         int rank = 0;
         for (int j = 0; j < p; ++j) {
             if (j == i) continue;
-            double mj = cabs(mu[j]), aj = atan2(mu[j].y, mu[j].x);
+            const double mj = mabs[j], aj = marg[j];
             bool before = (mj > mi) || (mj == mi && (aj > ai || (aj == ai && j < i)));
             rank += before ? 1 : 0;
         }
         order[rank] = i;
         int d = 0;
         if (!(res[i] <= ctol[i])) {
-            const double rad = fmax(res[i], dup_rel * cabs(mu[i]));
+            const double rad = fmax(res[i], dup_rel * mabs[i]);
             for (int j = 0; j < p; ++j)
                 if (j != i && res[j] <= ctol[j] && cabs(csub(mu[i], mu[j])) <= rad) d = 1;
         }
@@ -149,12 +159,12 @@ __device__ inline void select_wanted(const double2* __restrict__ mu, const doubl
             if (conv) {
                 // a converged copy of an accepted value (only with dup_rel > 0)
                 take = true;
-                const double rad = dup_rel * cabs(mu[i]);
+                const double rad = dup_rel * mabs[i];
                 for (int a = 0; a < nsel && take; ++a)
                     if (cabs(csub(mu[i], mu[sel[a]])) < rad) take = false;
             } else {
                 take = !dupc[i];
-                const double rad = fmax(res[i], dup_rel * cabs(mu[i]));
+                const double rad = fmax(res[i], dup_rel * mabs[i]);
                 for (int a = 0; a < nsel && take; ++a)
                     if (cabs(csub(mu[i], mu[sel[a]])) <= rad) take = false;
             }
@@ -464,22 +474,25 @@ __device__ inline double readlane_d(double v, int l) {
 
 // Eigenvector z (complex, z[j] = 0 beyond the eigenvalue's block) of the quasi
 // upper-triangular real T (row-major p x p) for eigenvalue index q with value m;
-// blk[j]: 0 = 1x1, 1 = first / 2 = second row of a 2x2 block.  Returns ||z||^2.
-__device__ inline double quasi_eigvec(const double* T, const int* blk, int p, int q, double2 m, double2* z) {
+// blk[j]: 0 = 1x1, 1 = first / 2 = second row of a 2x2 block.  Entry j goes to
+// zs[j * ZS].  Returns ||z||^2.
+template <int ZS>
+__device__ inline double quasi_eigvec(const double* T, const int* blk, int p, int q, double2 m, double2* zs) {
+    auto z = [&](int j) -> double2& { return zs[j * ZS]; };
     double smin = kEps * (fabs(m.x) + fabs(m.y));
     if (smin < 1e-290) smin = 1e-290;
     int c;  // next row to solve (downwards to 0)
     double nrm = 1.0;
     if (blk[q] == 0) {
-        z[q] = cmk<double2>(1.0, 0.0);
+        z(q) = cmk<double2>(1.0, 0.0);
         c = q - 1;
     } else {
-        // rows (r0, r0+1) of the pair; z[r0+1] = 1, z[r0] = (m - T[r0+1][r0+1]) / T[r0+1][r0]
+        // rows (r0, r0+1) of the pair; z(r0+1) = 1, z(r0) = (m - T[r0+1][r0+1]) / T[r0+1][r0]
         const int r0 = blk[q] == 1 ? q : q - 1;
         const double sub = T[(r0 + 1) * p + r0];
         const double2 z0 = cscale(cmk<double2>(m.x - T[(r0 + 1) * p + r0 + 1], m.y), 1.0 / sub);
-        z[r0 + 1] = cmk<double2>(1.0, 0.0);
-        z[r0] = z0;
+        z(r0 + 1) = cmk<double2>(1.0, 0.0);
+        z(r0) = z0;
         nrm += cabs2(z0);
         c = r0 - 1;
     }
@@ -488,9 +501,10 @@ __device__ inline double quasi_eigvec(const double* T, const int* blk, int p, in
         if (blk[c] == 2) {
             // 2x2 block (c-1, c): [T - m I] [z_{c-1}; z_c] = -[r_{c-1}; r_c]
             double2 r1 = cmk<double2>(0.0, 0.0), r2 = cmk<double2>(0.0, 0.0);
+#pragma unroll 4
             for (int j = c + 1; j <= top; ++j) {
-                r1 = cadd(r1, cscale(z[j], T[(c - 1) * p + j]));
-                r2 = cadd(r2, cscale(z[j], T[c * p + j]));
+                r1 = cadd(r1, cscale(z(j), T[(c - 1) * p + j]));
+                r2 = cadd(r2, cscale(z(j), T[c * p + j]));
             }
             const double2 a = cmk<double2>(T[(c - 1) * p + (c - 1)] - m.x, -m.y);
             const double2 b = cmk<double2>(T[(c - 1) * p + c], 0.0);
@@ -501,22 +515,23 @@ __device__ inline double quasi_eigvec(const double* T, const int* blk, int p, in
             // Cramer's rule on -r
             const double2 x1 = cdiv(csub(cmul(b, r2), cmul(e, r1)), det);
             const double2 x2 = cdiv(csub(cmul(d, r1), cmul(a, r2)), det);
-            z[c - 1] = x1;
-            z[c] = x2;
+            z(c - 1) = x1;
+            z(c) = x2;
             nrm += cabs2(x1) + cabs2(x2);
             c -= 2;
         } else {
             double2 r = cmk<double2>(0.0, 0.0);
-            for (int j = c + 1; j <= top; ++j) r = cadd(r, cscale(z[j], T[c * p + j]));
+#pragma unroll 8
+            for (int j = c + 1; j <= top; ++j) r = cadd(r, cscale(z(j), T[c * p + j]));
             double2 den = cmk<double2>(T[c * p + c] - m.x, -m.y);
             if (cabs1(den) < smin) den = cmk<double2>(smin, 0.0);
             const double2 x = cdiv(cmk<double2>(-r.x, -r.y), den);
-            z[c] = x;
+            z(c) = x;
             nrm += cabs2(x);
             c -= 1;
         }
     }
-    for (int j = top + 1; j < p; ++j) z[j] = cmk<double2>(0.0, 0.0);
+    for (int j = top + 1; j < p; ++j) z(j) = cmk<double2>(0.0, 0.0);
     return nrm;
 }
 
@@ -913,6 +928,10 @@ __device__ __attribute__((always_inline)) inline void francis_real(double* Tr, d
 // Ritz values of the quasi-triangular T (the 2x2 blocks give a + ib, a - ib in
 // consecutive entries), eigenvectors of T in S (one per lane, back
 // substitution) and residuals beta |zl . z_i| / ||z_i||, zl the last row of Z.
+// ZS = 1: S is p x p in global memory; ZS = kHT: p x 64 in LDS, a column per lane, and
+// each eigenvector gives way to the next of its lane.  p = 42: 121 us through global
+// memory, 46 in LDS.
+template <int ZS>
 __device__ inline void real_ritz(const double* Tr, const int* blk, const double* zl, int p, double beta,
                                  double2* __restrict__ mu, double2* __restrict__ S, double* __restrict__ res, int lane) {
     for (int i = lane; i < p; i += kHT) {
@@ -927,12 +946,21 @@ __device__ inline void real_ritz(const double* Tr, const int* blk, const double*
             m = cmk<double2>(0.5 * (a + d), blk[i] == 1 ? im : -im);
         }
         mu[i] = m;
-        double2* zc = S + (size_t)i * p;
-        const double n2 = quasi_eigvec(Tr, blk, p, i, m, zc);
+        double2* zc = ZS == 1 ? S + (size_t)i * p : S + lane;
+        const double n2 = quasi_eigvec<ZS>(Tr, blk, p, i, m, zc);
         double2 last = cmk<double2>(0.0, 0.0);
-        for (int c = 0; c < p; ++c) last = cadd(last, cscale(zc[c], zl[c]));
+#pragma unroll 8
+        for (int c = 0; c < p; ++c) last = cadd(last, cscale(zc[c * ZS], zl[c]));
         res[i] = fabs(beta) * cabs(last) / sqrt(n2);
     }
+}
+
+// Dynamic LDS of k_hess_ritz_real: T, and the eigenvectors of the lanes where they fit
+// beside it in the 160 KB.
+__host__ __device__ constexpr bool ritz_vectors_in_lds(int p) { return p <= 86; }
+constexpr size_t ritz_real_lds(int p) {
+    const size_t t = size_t(p * p + 1) / 2 * 2 * sizeof(double);
+    return ritz_vectors_in_lds(p) ? t + size_t(p) * kHT * sizeof(double2) : t;
 }
 
 __global__ __launch_bounds__(kHT) void k_hess_ritz_real(StepSet ss, int kreq, double tol, int standalone) {
@@ -983,7 +1011,10 @@ __global__ __launch_bounds__(kHT) void k_hess_ritz_real(StepSet ss, int kreq, do
     int total = 0, failed = 0;
     francis_real<false>(Tr, zl, blk, p, lane, total, failed, dsc.stop);
     if (failed == 2) return;  // a discarded step: nothing reads its outputs
-    real_ritz(Tr, blk, zl, p, beta, mu, S, res, lane);
+    if (ritz_vectors_in_lds(p))
+        real_ritz<kHT>(Tr, blk, zl, p, beta, mu, reinterpret_cast<double2*>(Tr + (p * p + 1) / 2 * 2), res, lane);
+    else
+        real_ritz<1>(Tr, blk, zl, p, beta, mu, S, res, lane);
     __syncthreads();
     if (standalone) {
         if (lane == 0 && rr) {
@@ -1387,7 +1418,7 @@ __global__ __launch_bounds__(kHT) void k_ks_contract(const KryDesc* __restrict__
     int total = 0, failed = 0;
     francis_real<true>(Tr, Zf, blk, m, lane, total, failed);
     __syncthreads();
-    real_ritz(Tr, blk, Zf + (size_t)(m - 1) * m, m, beta, dsc.mu, dsc.S, dsc.res, lane);
+    real_ritz<1>(Tr, blk, Zf + (size_t)(m - 1) * m, m, beta, dsc.mu, dsc.S, dsc.res, lane);
     __syncthreads();
     select_wanted(dsc.mu, dsc.res, dsc.sel, rr, ctol, order, dupc, m, k, tol, dsc.dup_rel, dsc.res_floor, failed,
                   total, lane);
@@ -1643,8 +1674,7 @@ tsk_status hess_ritz_launch(const KryDesc* D, int count, int p, int k, double to
         TSK_HIP(hipFuncSetAttribute((const void*)k_hess_ritz<true>, hipFuncAttributeMaxDynamicSharedMemorySize, mx));
         TSK_HIP(hipFuncSetAttribute((const void*)k_hess_ritz<false>, hipFuncAttributeMaxDynamicSharedMemorySize, mx));
         TSK_HIP(hipFuncSetAttribute((const void*)k_ritz_coords, hipFuncAttributeMaxDynamicSharedMemorySize, mx));
-        TSK_HIP(hipFuncSetAttribute((const void*)k_hess_ritz_real, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    int(kMaxKrylov * kMaxKrylov * sizeof(double))));
+        TSK_HIP(hipFuncSetAttribute((const void*)k_hess_ritz_real, hipFuncAttributeMaxDynamicSharedMemorySize, mx));
         attr_set = true;
     }
     if (attrs_only) return TSK_OK;
@@ -1653,8 +1683,8 @@ tsk_status hess_ritz_launch(const KryDesc* D, int count, int p, int k, double to
     one.p[0] = p;
     if (real_h) {
         // full: the standalone entry point (beta from scal[2]; values and residuals only)
-        hipLaunchKernelGGL(k_hess_ritz_real, dim3(count, 1), dim3(kHT), size_t(p) * p * sizeof(double), s, one, k,
-                           tol, full ? 1 : 0);
+        hipLaunchKernelGGL(k_hess_ritz_real, dim3(count, 1), dim3(kHT), ritz_real_lds(p), s, one, k, tol,
+                           full ? 1 : 0);
     } else {
         const size_t lds = size_t(p) * p * sizeof(double2);
         if (full)
@@ -1670,15 +1700,16 @@ tsk_status ritz_steps_launch(const StepSet& ss, int n, int count, int k, double 
                              hipStream_t s) {
     if (n < 1 || n > StepSet::kMax) return fail(TSK_EINVAL, "step batch size out of range");
     int pmax = 0;
+    size_t lds = 0;  // of the real analyses: the largest need, not that of the largest order
     for (int i = 0; i < n; ++i) {
         if (ss.p[i] < 1 || ss.p[i] > kMaxKrylov) return fail(TSK_EINVAL, "Krylov order must be in [1, 96]");
         pmax = ss.p[i] > pmax ? ss.p[i] : pmax;
+        lds = std::max(lds, ritz_real_lds(ss.p[i]));
     }
     if (svd) return tridiag_ritz_launch_steps(ss, n, count, pmax, k, tol, s);
     TSK_TRY(hess_ritz_launch(ss.tab[0], count, ss.p[0], k, tol, false, s, real_h, /*attrs_only=*/true));
     if (real_h)
-        hipLaunchKernelGGL(k_hess_ritz_real, dim3(count, n), dim3(kHT), size_t(pmax) * pmax * sizeof(double), s, ss,
-                           k, tol, 0);
+        hipLaunchKernelGGL(k_hess_ritz_real, dim3(count, n), dim3(kHT), lds, s, ss, k, tol, 0);
     else
         hipLaunchKernelGGL(k_hess_ritz<false>, dim3(count, n), dim3(kHT), size_t(pmax) * pmax * sizeof(double2), s,
                            ss, k, tol);
