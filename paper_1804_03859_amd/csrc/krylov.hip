@@ -73,7 +73,7 @@ template <typename T> __device__ inline T ldg(const T* p, int64_t i) {
 // load is in flight before the first wait, and accumulates each vector in the
 // element order e = 0, 1, ... (elements beyond the state skipped) before its
 // shuffle reduction.
-constexpr int kDotU = 8;
+constexpr int kDotU = 8;  // the values of one wave_sum8
 template <typename TS, typename A>
 __device__ inline void chunk_dots(const TS* __restrict__ V, int64_t ldv, int p, const A* wl, int64_t base,
                                   int64_t n, double2* __restrict__ partial) {
@@ -97,29 +97,29 @@ __device__ inline void chunk_dots(const TS* __restrict__ V, int64_t ldv, int p, 
                 vv[u][e] = ldg(vi, l < lim ? l : lim - 1);
             }
         }
-        double2 a[U];
+        // real states: eight sums; complex: four, real and imaginary parts
+        double s[8];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            a[u] = cmk<double2>(0.0, 0.0);
+            double2 a = cmk<double2>(0.0, 0.0);
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                if (lane + e * kWave < lim) a[u] = cadd(a[u], dotc(vv[u][e], wv[e]));
-            if constexpr (kReal)
-                a[u].x = wave_sum(a[u].x);  // the imaginary parts are exact zeros
-            else
-                a[u] = wave_sum(a[u]);
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + NW * u;
-                if (i < p) {
-                    if constexpr (kReal)  // real partials: half the bytes for every block to reduce
-                        reinterpret_cast<double*>(partial)[size_t(blockIdx.x) * p + i] = a[u].x;
-                    else
-                        partial[size_t(blockIdx.x) * p + i] = a[u];
-                }
+                if (lane + e * kWave < lim) a = cadd(a, dotc(vv[u][e], wv[e]));
+            if constexpr (kReal) {
+                s[u] = a.x;  // the imaginary parts are exact zeros
+            } else {
+                s[2 * u] = a.x;
+                s[2 * u + 1] = a.y;
             }
+        }
+        const double t = wave_sum8(s);
+        const int v = wave_sum8_index(lane), i = i0 + NW * (kReal ? v : v >> 1);
+        if ((lane & 7) == 0 && i < p) {
+            double* out = reinterpret_cast<double*>(partial);
+            if constexpr (kReal)  // real partials: half the bytes for every block to reduce
+                out[size_t(blockIdx.x) * p + i] = t;
+            else
+                out[2 * (size_t(blockIdx.x) * p + i) + (v & 1)] = t;
         }
     }
 }
@@ -209,13 +209,16 @@ __global__ __launch_bounds__(kBT) void k_dot(const KryDesc* __restrict__ Dv, int
 // by one wavefront: per coefficient, lanes over blocks in a fixed order, then a
 // shuffle tree, so every block of a fused pass gets the same bits.  The loads
 // of the kDotU coefficients overlap.  REAL: the partials are stored as doubles
-// (real states), the imaginary parts of the results exact zeros.
+// (real states), the imaginary parts of the results exact zeros.  The lane gets
+// coefficient i0 + stride wave_sum8_index(lane).  (One wave_sum per part and
+// coefficient instead: a pass at 128^2 FP64, 40 vectors, 13 and 15 us, now 9 and 12;
+// k_dot 6.5, now 5.5.)
 template <bool REAL>
-__device__ inline void reduce_coefs(const double2* __restrict__ partial, int nblk, int p, int i0, int stride,
-                                   int lane, double2 (&out)[kDotU]) {
-    double2 sv[kDotU];
+__device__ inline double2 reduce_coefs(const double2* __restrict__ partial, int nblk, int p, int i0, int stride,
+                                       int lane) {
+    double sx[kDotU], sy[kDotU];
 #pragma unroll
-    for (int u = 0; u < kDotU; ++u) sv[u] = cmk<double2>(0.0, 0.0);
+    for (int u = 0; u < kDotU; ++u) sx[u] = sy[u] = 0.0;
     for (int b = lane; b < nblk; b += kWave) {
         double2 t[kDotU];
 #pragma unroll
@@ -228,10 +231,12 @@ __device__ inline void reduce_coefs(const double2* __restrict__ partial, int nbl
                 t[u] = ldg(partial, at);
         }
 #pragma unroll
-        for (int u = 0; u < kDotU; ++u) sv[u] = cadd(sv[u], t[u]);
+        for (int u = 0; u < kDotU; ++u) {
+            sx[u] += t[u].x;
+            if constexpr (!REAL) sy[u] += t[u].y;
+        }
     }
-#pragma unroll
-    for (int u = 0; u < kDotU; ++u) out[u] = wave_sum(sv[u]);
+    return cmk<double2>(wave_sum8(sx), REAL ? 0.0 : wave_sum8(sy));
 }
 __device__ inline double reduce_norm(const double* __restrict__ pn, int nblk, int lane) {
     double s = 0.0;
@@ -295,19 +300,13 @@ __device__ inline void reduce_pass_coefs(const KryDesc& d, int p, int j, int pas
     double2* Hcol = d.H + size_t(d.ldh) * j;
     constexpr int NW = kBT / kWave;
     for (int i0 = w0; i0 < p; i0 += wstride * kDotU) {
-        double2 sv[kDotU];
-        reduce_coefs<!std::is_same<TS, double2>::value>(pin, d.nblk, p, i0, NW, lane, sv);
-        if (lane == 0) {
-#pragma unroll
-            for (int u = 0; u < kDotU; ++u) {
-                const int i = i0 + NW * u;
-                if (i < p) {
-                    if (hl) hl[i] = sv[u];
-                    if (write_h) {
-                        Hcol[i] = pass == 1 ? sv[u] : cadd(Hcol[i], sv[u]);
-                        d.h[i] = sv[u];
-                    }
-                }
+        const double2 c = reduce_coefs<!std::is_same<TS, double2>::value>(pin, d.nblk, p, i0, NW, lane);
+        const int i = i0 + NW * wave_sum8_index(lane);
+        if ((lane & 7) == 0 && i < p) {
+            if (hl) hl[i] = c;
+            if (write_h) {
+                Hcol[i] = pass == 1 ? c : cadd(Hcol[i], c);
+                d.h[i] = c;
             }
         }
     }
