@@ -16,6 +16,11 @@
 // loss, bias gradients and Adam are FP32 vector kernels.  Loss and bias sums
 // are reduced in a fixed order, so a training run is reproducible bit for bit.
 //
+// A training step is bound by its launches (B = 64, W = 512: 93 us in 17 of them, against
+// some 7 us of Adam traffic), so what does not depend on each other shares one: 10
+// launches, 60 us (k_layer_back, the slabs of the output layer summed by
+// k_loss, the first layer's gradient beside the Adam step).
+//
 // Parameter vector layout (flat, FP32): W1 [2][W], b1 [W], W2 [W][W], b2 [W],
 // W3 [W][2048], b3 [2048], weights row-major [in][out].
 #include <algorithm>
@@ -95,13 +100,12 @@ __device__ inline void gemm_epilogue(const GemmArgs& g, int row, int col, float 
 // element by element.  The next slice's global loads are issued before the
 // current slice's products, so they overlap.
 template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g, GemmSplit sp) {
-    __shared__ __align__(16) uint16_t As[GT * GLD];
-    __shared__ __align__(16) uint16_t Bs[GT * GLD];
+__device__ inline void gemm_tile(const GemmArgs& g, const GemmSplit& sp, int bx, int by, int bz, uint16_t* As,
+                                 uint16_t* Bs) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
+    const int m0 = by * GT, n0 = bx * GT;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int kbeg = sp.part ? int(blockIdx.z) * sp.kslab : 0;
+    const int kbeg = sp.part ? bz * sp.kslab : 0;
     const int kend = sp.part ? min(g.K, kbeg + sp.kslab) : g.K;
     // 16-byte loads need 16-byte aligned rows (k0 is a multiple of 8)
     const bool avec = ((reinterpret_cast<uintptr_t>(g.A) | (uintptr_t(g.lda) * 2)) & 15) == 0;
@@ -197,10 +201,40 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g, GemmSplit sp) {
                 const int col = n0 + wn + 16 * j + (lane & 15);
                 if (row >= g.M || col >= g.N) continue;
                 if (sp.part)
-                    sp.part[(size_t(blockIdx.z) * g.M + row) * g.N + col] = acc[i][j][r];
+                    sp.part[(size_t(bz) * g.M + row) * g.N + col] = acc[i][j][r];
                 else
                     gemm_epilogue<EPI>(g, row, col, acc[i][j][r]);
             }
+}
+
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void k_gemm(GemmArgs g, GemmSplit sp) {
+    __shared__ __align__(16) uint16_t As[GT * GLD];
+    __shared__ __align__(16) uint16_t Bs[GT * GLD];
+    gemm_tile<TA, TB, EPI>(g, sp, blockIdx.x, blockIdx.y, blockIdx.z, As, Bs);
+}
+
+// The split-K sums of U elements, in slab order; the loads of four slabs overlap.
+template <int U>
+__device__ inline void slab_sums(const float* __restrict__ part, int splits, int64_t count, const int64_t (&e)[U],
+                                 float (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = 0.0f;
+    int z = 0;
+    for (; z + 4 <= splits; z += 4) {
+        float p[4][U];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u) p[i][u] = part[size_t(z + i) * count + e[u]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] += p[i][u];
+    }
+    for (; z < splits; ++z)
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] += part[size_t(z) * count + e[u]];
 }
 
 // Sum of the split-K slabs in slab order, then the epilogue.
@@ -208,9 +242,10 @@ template <int EPI>
 __global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs g, const float* __restrict__ part, int splits) {
     const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (e >= int64_t(g.M) * g.N) return;
-    float v = 0.0f;
-    for (int z = 0; z < splits; ++z) v += part[size_t(z) * g.M * g.N + e];
-    gemm_epilogue<EPI>(g, int(e / g.N), int(e % g.N), v);
+    const int64_t at[1] = {e};
+    float v[1];
+    slab_sums(part, splits, int64_t(g.M) * g.N, at, v);
+    gemm_epilogue<EPI>(g, int(e / g.N), int(e % g.N), v[0]);
 }
 
 // Split K when the tile grid is small (< 64 workgroups) and K long: slabs of at
@@ -223,20 +258,26 @@ inline int gemm_splits(int M, int N, int K) {
     return s;
 }
 
+inline GemmSplit gemm_split(const GemmArgs& g, int splits, float* work) {
+    if (splits <= 1) return GemmSplit{nullptr, g.K};
+    return GemmSplit{work, ((g.K + splits - 1) / splits + GK - 1) / GK * GK};
+}
+
+template <int EPI> void gemm_reduce(const GemmArgs& g, const float* work, int splits, hipStream_t s) {
+    if (splits <= 1) return;
+    const int64_t ne = int64_t(g.M) * g.N;
+    hipLaunchKernelGGL(k_gemm_reduce<EPI>, dim3(unsigned((ne + 255) / 256)), dim3(256), 0, s, g, work, splits);
+}
+
+// reduce = false: leaves the slabs of a split product in `work` to its reader.
+// Returns the number of slabs.
 template <bool TA, bool TB, int EPI>
-void gemm(const GemmArgs& g, float* work, hipStream_t s) {
+int gemm(const GemmArgs& g, float* work, hipStream_t s, bool reduce = true) {
     const int splits = work ? gemm_splits(g.M, g.N, g.K) : 1;
-    GemmSplit sp{nullptr, g.K};
-    if (splits > 1) {
-        sp.part = work;
-        sp.kslab = ((g.K + splits - 1) / splits + GK - 1) / GK * GK;
-    }
     dim3 grid((g.N + GT - 1) / GT, (g.M + GT - 1) / GT, splits);
-    hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, g, sp);
-    if (splits > 1) {
-        const int64_t ne = int64_t(g.M) * g.N;
-        hipLaunchKernelGGL(k_gemm_reduce<EPI>, dim3(unsigned((ne + 255) / 256)), dim3(256), 0, s, g, work, splits);
-    }
+    hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, g, gemm_split(g, splits, work));
+    if (reduce) gemm_reduce<EPI>(g, work, splits, s);
+    return splits;
 }
 
 // ---- vector kernels -------------------------------------------------------------------
@@ -262,18 +303,46 @@ __global__ void k_l1_fwd(const float* __restrict__ in, int B, int W, const float
 
 constexpr int kLossBlocks = 64;
 
-// dY = scale (Y - T); per-block partial sums of (Y - T)^2 in FP64.
-__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ Y, const float* __restrict__ T,
+// dY = scale (Y - T); per-block partial sums of (Y - T)^2 in FP64.  splits > 1: Y is
+// still in slabs (of the output layer's product, bias to come) and is stored too.  Bound
+// by the latency of its loads: 4.4 us with eight elements' four slabs in flight, 17.4 with
+// one after the other (B = 64); the slab sum and the loss apart 3.3 + 5.8.
+__global__ __launch_bounds__(256) void k_loss(float* __restrict__ Y, const float* __restrict__ T,
                                               int64_t count, float scale, float* __restrict__ dY,
-                                              uint16_t* __restrict__ dYh, double* __restrict__ partial) {
+                                              uint16_t* __restrict__ dYh, double* __restrict__ partial,
+                                              const float* __restrict__ part, int splits,
+                                              const float* __restrict__ bias) {
     __shared__ double red[256];
+    // U elements at a time (a thread's terms stay in element order): their loads overlap
+    constexpr int U = 8;
     double acc = 0.0;
-    for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < count; e += int64_t(gridDim.x) * blockDim.x) {
-        const float d = Y[e] - T[e];
-        acc += double(d) * double(d);
-        const float gd = scale * d;
-        dY[e] = gd;
-        dYh[e] = f2bf(gd);
+    const int64_t st = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t e0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e0 < count; e0 += U * st) {
+        int64_t e[U];
+        float y[U], t[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            e[u] = e0 + u * st < count ? e0 + u * st : count - 1;
+            t[u] = T[e[u]];
+        }
+        if (splits > 1) {
+            slab_sums(part, splits, count, e, y);
+#pragma unroll
+            for (int u = 0; u < U; ++u) y[u] += bias[e[u] % kOut];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) y[u] = Y[e[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e0 + u * st >= count) break;
+            if (splits > 1) Y[e[u]] = y[u];
+            const float d = y[u] - t[u];
+            acc += double(d) * double(d);
+            const float gd = scale * d;
+            dY[e[u]] = gd;
+            dYh[e[u]] = f2bf(gd);
+        }
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -284,20 +353,17 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ Y, const
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ void k_loss_final(const double* __restrict__ partial, int nb, double inv_count, double* out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < nb; ++i) s += partial[i];
-        *out = s * inv_count;
-    }
+__device__ inline void loss_total(const double* __restrict__ partial, double inv_count, double* out) {
+    double s = 0.0;
+#pragma unroll 16
+    for (int i = 0; i < kLossBlocks; ++i) s += partial[i];
+    *out = s * inv_count;
 }
 
 // g[n] = sum_b D[b][n] (FP64 accumulation, rows in order).  Rows are loaded
 // eight at a time ahead of the additions (the sum stays in row order), so the
 // loads overlap instead of each waiting for the previous addition.
-__global__ void k_colsum(const float* __restrict__ D, int B, int N, float* __restrict__ g) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+__device__ inline void colsum(const float* __restrict__ D, int B, int N, int n, float* __restrict__ g) {
     double s = 0.0;
     int b = 0;
     for (; b + 8 <= B; b += 8) {
@@ -311,12 +377,44 @@ __global__ void k_colsum(const float* __restrict__ D, int B, int N, float* __res
     g[n] = float(s);
 }
 
+// The back-products of one layer, which all read the deltas D (B x N) above it, in one
+// launch of 256-thread workgroups: the tiles of the weight gradient A^T D (never split),
+// those of the delta below, D W^T (slabs if sp.part), the bias gradient, and with `out` the
+// loss.  One after the other they were four launches of 4 to 6 us, together 8.6 (output
+// layer) and 5.7 us; bound: the latency of one delta tile.
+struct LayerBack {
+    GemmArgs gw, gd;
+    GemmSplit sp;
+    int wx, wtiles;          // weight gradient: tiles along x, all
+    int dx, dy, dtiles;      // delta: tiles along x and y, all (slabs included)
+    const float* D;
+    float* gb;
+    int B, N, sums;          // bias gradient: workgroups
+    const double* partial;
+    double inv_count;
+    double* out;
+};
+__global__ __launch_bounds__(256) void k_layer_back(LayerBack a) {
+    __shared__ __align__(16) uint16_t As[GT * GLD];
+    __shared__ __align__(16) uint16_t Bs[GT * GLD];
+    int b = int(blockIdx.x);
+    if (b < a.dtiles) {  // the longest first
+        gemm_tile<false, true, EPI_DTANH>(a.gd, a.sp, b % a.dx, b / a.dx % a.dy, b / (a.dx * a.dy), As, Bs);
+    } else if ((b -= a.dtiles) < a.wtiles) {
+        gemm_tile<true, false, EPI_STORE>(a.gw, GemmSplit{nullptr, a.gw.K}, b % a.wx, b / a.wx, 0, As, Bs);
+    } else if ((b -= a.wtiles) < a.sums) {
+        // 64 columns per workgroup: the sums are serial, so they spread out
+        const int n = b * 64 + int(threadIdx.x);
+        if (threadIdx.x < 64 && n < a.N) colsum(a.D, a.B, a.N, n, a.gb);
+    } else if (threadIdx.x == 0) {
+        loss_total(a.partial, a.inv_count, a.out);
+    }
+}
+
 // gW1[i][n] = sum_b X[b][i] dZ1[b][n], gb1[n] = sum_b dZ1[b][n] (rows in order,
-// loaded eight at a time as in k_colsum).
-__global__ void k_l1_grad(const float* __restrict__ X, const float* __restrict__ dZ1, int B, int W,
-                          float* __restrict__ grad) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= W) return;
+// loaded eight at a time as in colsum).
+__device__ inline void l1_grad(const float* __restrict__ X, const float* __restrict__ dZ1, int B, int W, int n,
+                               float* __restrict__ grad) {
     double s0 = 0.0, s1 = 0.0, sb = 0.0;
     int b = 0;
     for (; b + 8 <= B; b += 8) {
@@ -347,19 +445,43 @@ __global__ void k_l1_grad(const float* __restrict__ X, const float* __restrict__
 
 // Adam (Kingma & Ba 2015) with bias corrections c1 = 1/(1-b1^t), c2 = 1/(1-b2^t);
 // refreshes the bfloat16 copy.
-__global__ void k_adam(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, int64_t count, float lr, float b1, float b2, float eps, float c1,
-                       float c2, uint16_t* __restrict__ wh) {
-    for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < count; e += int64_t(gridDim.x) * blockDim.x) {
-        const float ge = g[e];
-        const float me = b1 * m[e] + (1.0f - b1) * ge;
-        const float ve = b2 * v[e] + (1.0f - b2) * ge * ge;
-        m[e] = me;
-        v[e] = ve;
-        const float we = w[e] - lr * (me * c1) / (sqrtf(ve * c2) + eps);
-        w[e] = we;
-        wh[e] = f2bf(we);
+struct AdamArgs {
+    float* w;
+    const float* g;
+    float* m;
+    float* v;
+    int64_t count;
+    float lr, b1, b2, eps, c1, c2;
+    uint16_t* wh;
+};
+// (a.w null: no step, the gradient alone)
+__device__ inline void adam_at(const AdamArgs& a, int64_t e) {
+    const float ge = a.g[e];
+    const float me = a.b1 * a.m[e] + (1.0f - a.b1) * ge;
+    const float ve = a.b2 * a.v[e] + (1.0f - a.b2) * ge * ge;
+    a.m[e] = me;
+    a.v[e] = ve;
+    const float we = a.w[e] - a.lr * (me * a.c1) / (sqrtf(ve * a.c2) + a.eps);
+    a.w[e] = we;
+    a.wh[e] = f2bf(we);
+}
+
+// The first layer's gradient and its Adam step by the first `first` workgroups (64
+// columns each, a serial sum per column), the Adam step of everything behind it by the
+// others meanwhile.
+__global__ __launch_bounds__(256) void k_l1_grad_adam(const float* __restrict__ X, const float* __restrict__ dZ1,
+                                                      int B, int W, float* grad, int first, AdamArgs a) {
+    if (int(blockIdx.x) < first) {
+        const int n = int(blockIdx.x) * 64 + int(threadIdx.x);
+        if (threadIdx.x >= 64 || n >= W) return;
+        l1_grad(X, dZ1, B, W, n, grad);
+        if (a.w)
+            for (int i = 0; i < 3; ++i) adam_at(a, int64_t(i) * W + n);
+        return;
     }
+    const int64_t st = int64_t(gridDim.x - first) * blockDim.x;
+    for (int64_t e = 3ll * W + int64_t(blockIdx.x - first) * blockDim.x + threadIdx.x; e < a.count; e += st)
+        adam_at(a, e);
 }
 
 __global__ void k_to_bf16(const float* __restrict__ w, uint16_t* __restrict__ wh, int64_t count) {
@@ -653,8 +775,10 @@ struct Mlp {
     float* wf() const { return w.as<float>(); }
     const uint16_t* whp(int64_t off) const { return wh.as<uint16_t>() + off; }
 
-    // Forward pass; Y (B x 2048) lands in `out` (may be the internal Y buffer).
-    void forward(const float* in, int B, float* out, hipStream_t s) {
+    // Forward pass; Y (B x 2048) lands in `out` (may be the internal Y buffer), or with
+    // slabs = true stays in gwork, without the bias, where its product was split.  Returns
+    // the number of slabs.
+    int forward(const float* in, int B, float* out, hipStream_t s, bool slabs = false) {
         const float sc0 = float(2.0 / (hi[0] - lo[0])), sc1 = float(2.0 / (hi[1] - lo[1]));
         hipLaunchKernelGGL(k_l1_fwd, dim3(grid_for(int64_t(B) * W)), dim3(256), 0, s, in, B, W, wf(), float(lo[0]),
                            sc0, float(lo[1]), sc1, X.as<float>(), A1.as<float>(), A1h.as<uint16_t>());
@@ -665,47 +789,77 @@ struct Mlp {
         GemmArgs b{};
         b.A = A2h.as<uint16_t>(); b.B = whp(o_W3); b.M = B; b.N = kOut; b.K = W;
         b.lda = W; b.ldb = kOut; b.ldc = kOut; b.C = out; b.bias = wf() + o_b3;
-        gemm<false, false, EPI_BIAS>(b, gwork.as<float>(), s);
+        return gemm<false, false, EPI_BIAS>(b, gwork.as<float>(), s, !slabs);
     }
 
-    // Loss into loss[slot] and the full gradient into g.
-    void backward(const float* target, int B, int slot, hipStream_t s) {
+    // The back-products of one layer (k_layer_back), and the delta's slabs summed.
+    void layer_back(const GemmArgs& gw, const GemmArgs& gd, const float* D, float* gb, bool total, int slot,
+                    int64_t cnt, hipStream_t s) {
+        LayerBack a{};
+        float* work = gwork.as<float>();
+        const bool own = gemm_splits(gw.M, gw.N, gw.K) > 1;  // small layers, large batches
+        if (own) gemm<true, false, EPI_STORE>(gw, work, s);
+        const int splits = gemm_splits(gd.M, gd.N, gd.K);
+        a.gw = gw;
+        a.gd = gd;
+        a.sp = gemm_split(gd, splits, work);
+        a.wx = (gw.N + GT - 1) / GT;
+        a.wtiles = own ? 0 : a.wx * ((gw.M + GT - 1) / GT);
+        a.dx = (gd.N + GT - 1) / GT;
+        a.dy = (gd.M + GT - 1) / GT;
+        a.dtiles = a.dx * a.dy * splits;
+        a.D = D;
+        a.gb = gb;
+        a.B = gw.K;
+        a.N = gw.N;
+        a.sums = (gw.N + 63) / 64;
+        a.partial = partial.as<double>();
+        a.inv_count = 1.0 / double(cnt);
+        a.out = loss.as<double>() + slot;
+        hipLaunchKernelGGL(k_layer_back, dim3(a.dtiles + a.wtiles + a.sums + (total ? 1 : 0)), dim3(256), 0, s, a);
+        gemm_reduce<EPI_DTANH>(gd, work, splits, s);
+    }
+
+    // Loss into loss[slot] and the gradient into g, except the first layer's (first_grad);
+    // splits: what forward() returned.
+    void backward(const float* target, int B, int slot, int splits, hipStream_t s) {
         const int64_t cnt = int64_t(B) * kOut;
         hipLaunchKernelGGL(k_loss, dim3(kLossBlocks), dim3(256), 0, s, Y.as<float>(), target, cnt,
-                           float(2.0 / double(cnt)), dY.as<float>(), dYh.as<uint16_t>(), partial.as<double>());
-        hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, partial.as<double>(), kLossBlocks,
-                           1.0 / double(cnt), loss.as<double>() + slot);
+                           float(2.0 / double(cnt)), dY.as<float>(), dYh.as<uint16_t>(), partial.as<double>(),
+                           gwork.as<float>(), splits, wf() + o_b3);
         float* G = g.as<float>();
         GemmArgs g3{};  // gW3 = A2h^T dYh
         g3.A = A2h.as<uint16_t>(); g3.B = dYh.as<uint16_t>(); g3.M = W; g3.N = kOut; g3.K = B;
         g3.lda = W; g3.ldb = kOut; g3.ldc = kOut; g3.C = G + o_W3;
-        gemm<true, false, EPI_STORE>(g3, gwork.as<float>(), s);
-        hipLaunchKernelGGL(k_colsum, dim3((kOut + 63) / 64), dim3(64), 0, s, dY.as<float>(), B, kOut, G + o_b3);
         GemmArgs d2{};  // dZ2 = (dYh W3h^T) * (1 - A2^2)
         d2.A = dYh.as<uint16_t>(); d2.B = whp(o_W3); d2.M = B; d2.N = W; d2.K = kOut;
         d2.lda = kOut; d2.ldb = kOut; d2.ldc = W; d2.C = dZ2.as<float>(); d2.Ch = dZ2h.as<uint16_t>();
         d2.act = A2.as<float>();
-        gemm<false, true, EPI_DTANH>(d2, gwork.as<float>(), s);
+        layer_back(g3, d2, dY.as<float>(), G + o_b3, true, slot, cnt, s);
         GemmArgs g2{};  // gW2 = A1h^T dZ2h
         g2.A = A1h.as<uint16_t>(); g2.B = dZ2h.as<uint16_t>(); g2.M = W; g2.N = W; g2.K = B;
         g2.lda = W; g2.ldb = W; g2.ldc = W; g2.C = G + o_W2;
-        gemm<true, false, EPI_STORE>(g2, gwork.as<float>(), s);
-        hipLaunchKernelGGL(k_colsum, dim3((W + 63) / 64), dim3(64), 0, s, dZ2.as<float>(), B, W, G + o_b2);
         GemmArgs d1{};  // dZ1 = (dZ2h W2h^T) * (1 - A1^2)
         d1.A = dZ2h.as<uint16_t>(); d1.B = whp(o_W2); d1.M = B; d1.N = W; d1.K = W;
         d1.lda = W; d1.ldb = W; d1.ldc = W; d1.C = dZ1.as<float>(); d1.act = A1.as<float>();
-        gemm<false, true, EPI_DTANH>(d1, gwork.as<float>(), s);
-        hipLaunchKernelGGL(k_l1_grad, dim3((W + 63) / 64), dim3(64), 0, s, X.as<float>(), dZ1.as<float>(), B, W,
-                           G + o_W1);
+        layer_back(g2, d1, dZ2.as<float>(), G + o_b2, false, slot, cnt, s);
     }
 
-    void adam(double lr, hipStream_t s) {
+    // The first layer's gradient, and with adam the step of all parameters.
+    void first_grad(int B, const AdamArgs* adam, hipStream_t s) {
+        const int first = (W + 63) / 64;
+        const AdamArgs a = adam ? *adam : AdamArgs{};
+        hipLaunchKernelGGL(k_l1_grad_adam, dim3(first + (adam ? grid_for(np) : 0)), dim3(256), 0, s, X.as<float>(),
+                           dZ1.as<float>(), B, W, g.as<float>() + o_W1, first, a);
+    }
+
+    AdamArgs adam_step(double lr) {
         ++t;
         const double b1 = 0.9, b2 = 0.999;
         const float c1 = float(1.0 / (1.0 - std::pow(b1, double(t))));
         const float c2 = float(1.0 / (1.0 - std::pow(b2, double(t))));
-        hipLaunchKernelGGL(k_adam, dim3(grid_for(np)), dim3(256), 0, s, wf(), g.as<float>(), m.as<float>(),
-                           v.as<float>(), np, float(lr), float(b1), float(b2), 1e-8f, c1, c2, wh.as<uint16_t>());
+        return AdamArgs{wf(), g.as<float>(), m.as<float>(), v.as<float>(), np, float(lr), float(b1), float(b2),
+                        1e-8f, c1, c2, wh.as<uint16_t>()};
     }
 
     tsk_status reset_optimizer() {
@@ -785,8 +939,9 @@ tsk_status mlp_forward(Mlp* n, const float* in, int B, float* out) {
 tsk_status mlp_gradients(Mlp* n, const float* in, const float* target, int B, float* grad, double* loss_host) {
     TSK_TRY(check_batch(n, B));
     TSK_TRY(n->reserve(B, 1));
-    n->forward(in, B, n->Y.as<float>(), n->stream);
-    n->backward(target, B, 0, n->stream);
+    const int slabs = n->forward(in, B, n->Y.as<float>(), n->stream, true);
+    n->backward(target, B, 0, slabs, n->stream);
+    n->first_grad(B, nullptr, n->stream);
     TSK_HIP(hipGetLastError());
     if (grad) TSK_HIP(hipMemcpyAsync(grad, n->g.ptr, size_t(n->np) * 4, hipMemcpyDeviceToDevice, n->stream));
     if (loss_host) TSK_HIP(hipMemcpyAsync(loss_host, n->loss.ptr, 8, hipMemcpyDeviceToHost, n->stream));
@@ -800,9 +955,10 @@ tsk_status mlp_train(Mlp* n, const float* in, const float* target, int B, int st
     if (!(lr > 0.0) || !std::isfinite(lr)) return fail(TSK_EINVAL, "learning rate must be positive");
     TSK_TRY(n->reserve(B, steps));
     for (int i = 0; i < steps; ++i) {
-        n->forward(in, B, n->Y.as<float>(), n->stream);
-        n->backward(target, B, i, n->stream);
-        n->adam(lr, n->stream);
+        const int slabs = n->forward(in, B, n->Y.as<float>(), n->stream, true);
+        n->backward(target, B, i, slabs, n->stream);
+        const AdamArgs a = n->adam_step(lr);
+        n->first_grad(B, &a, n->stream);
     }
     TSK_HIP(hipGetLastError());
     if (loss_host)
