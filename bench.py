@@ -76,10 +76,10 @@ def power_tiles(N, nh=4):
 
 
 def integrates_by_squaring(N, nsteps, fp32, nh=4):
-    """Whether a plain matvec of a one-harmonic base flow squares the step matrix of
+    """Whether a plain forward matvec of a one-harmonic base flow squares the step matrix of
     its chains (the library's rule: step counts by tiles of 16 modes)."""
     t = power_tiles(N, nh)
-    least = ((16, 24, 56, None, 80, 80) if fp32 else (16, 28, 72, 176, 120, 120))
+    least = ((24, 32, 64, None, 80, 80) if fp32 else (16, 32, 76, 176, 140, 140))
     return t <= 6 and 1 + (N - 1) // 3 * (nh // 2 + 1) <= 768 and least[t - 1] is not None and nsteps >= least[t - 1]
 
 
@@ -143,7 +143,7 @@ def cpu_baseline(seconds=12.0):
 
 
 COLSTEP_SOURCES = ("common.hpp", "colstep.hpp", "colcouple.hpp")
-GENERAL_SOURCES = ("common.hpp", "fft.hpp", "kolmo2d.hip")
+GENERAL_SOURCES = ("common.hpp", "fft.hpp", "genflow.hpp", "kolmo2d.hip")
 
 
 def measured_traffic(profile_name, sources=COLSTEP_SOURCES, key="traffic_bytes_per_launch"):
@@ -435,15 +435,19 @@ def run_optimal(args, tsk, W, np, torch):
 
 
 def general_stage_bytes(N, s):
-    """Algorithmic HBM bytes of one RK4 stage of the general base-flow pipeline
-    (s bytes per real): the row kernel reads the four derived fields G
-    (4 x (M+1) x N complex) and the four base fields (4 N^2 reals) and writes the
-    product spectrum Q ((M+1) x N complex); the column kernel reads Q, reads and
-    writes the packed state and RK4 accumulator (n reals each) and writes G."""
+    """Algorithmic bytes of one RK4 stage of the general base-flow pipeline (s bytes
+    per real), row and column side.  Up to 256^2 (one launch per integration) the
+    workgroups exchange the four derived fields G (4 x (M+1) x N complex) and the
+    product spectrum Q ((M+1) x N complex) as tagged words of twice their size; the
+    rest stays on the chip.  Beyond, the row kernel reads G and the four base fields
+    (4 N^2 reals) and writes Q; the column kernel reads Q, reads and writes the
+    packed state and RK4 accumulator (n reals each) and writes G."""
     M = (N - 1) // 3
     n = 4 * M * (M + 1)
     g = 4 * (M + 1) * N * 2 * s
     q = (M + 1) * N * 2 * s
+    if N <= 256:
+        return 2 * (g + q), 2 * (g + q)
     row = g + 4 * N * N * s + q
     col = q + g + 4 * n * s
     return row, col
@@ -519,7 +523,7 @@ def run_fixed_point(args, tsk, W, np, torch):
                            "time_steps": sf["time_steps"], "ms": sf["ms_total"], "status": sf["status"]},
                    "rpm_vs_boostconv_rel_diff": agree, "fixed_point_distance_from_laminar_rel": dist,
                    "ms_per_G": g_ms},
-        "roofline": {"bound": "hbm", "kernel": "k_gen_row<double,128,ROW_NL> + k_gen_col<double,128> (nonlinear step)",
+        "roofline": {"bound": "hbm", "kernel": "k_flow<double,128,true> (nonlinear steps, all stages in one launch)",
                      "achieved": achieved, "peak": 8000.0, "unit": "GB/s", "frac": achieved / 8000.0,
                      "bytes_per_G": bytes_g, "traffic": None},
         "cpu_baseline": None,
@@ -570,7 +574,7 @@ def run_general(args, tsk, W, np, torch):
                                "Arnoldi m=64 k=6 tol=1e-8, full 2-D pseudo-spectral pipeline",
                    "n_matvec": nmv, "status": r["status"], "ms_per_matvec": ms_apply / nmv,
                    "lambda": [[round(float(v.real), 10), round(float(v.imag), 10)] for v in r["lam"]]},
-        "roofline": {"bound": "hbm", "kernel": "k_gen_row<double,128> + k_gen_col<double,128> (time stepper)",
+        "roofline": {"bound": "hbm", "kernel": "k_flow<double,128,false> (time stepper, all stages in one launch)",
                      "achieved": achieved, "peak": 8000.0, "unit": "GB/s", "frac": achieved / 8000.0,
                      "bytes_per_matvec": bytes_per_matvec,
                      "traffic": None if stage_traffic is None else stage_traffic * 4 * nsteps},

@@ -538,25 +538,31 @@ tsk_status couple_choice(const CoupleKey& key, hipStream_t s, F&& launch, int* o
 // longest chain has ceil((2M + 1) / nh) modes.
 inline int couple_slots(int M, int nh) { return ((2 * M + 1 + nh - 1) / nh + kWave - 1) / kWave; }
 
-// Squaring (colpower.hpp) or stepping: the smallest step count at which a single
-// matvec by squaring is the faster one, by the tiles of the longest chain.
-// Stepping / squaring in us, FP64 (FP32), 4 chains per column: 96^2 (1 tile) 16
-// steps 5.1 / 5.1 (4.6 / 4.7), 32 steps 7.3 / 5.4 (6.2 / 4.9); 128^2 (2) 16 steps
-// 5.1 / 6.1, 32 steps 7.3 / 6.7, 200 steps 30.3 / 9.0 (23.5 / 7.2); 256^2 (3) 64 steps
-// 11.9 / 12.1 (9.6 / 9.1), 200 steps 30.4 / 15.4 (23.6 / 11.4); 384^2 (4) 100 steps
-// 17.7 / 23.6, 200 steps 31.4 / 28.4; 512^2 (6) 100 steps 45.0 / 47.4 (29.0 / 25.1), 200
-// steps 84.8 / 64.9 (52.9 / 34.5).  FP32 chains of 4 tiles step: 384^2 alone would
-// gain (24.0 / 19.3), but a batch fills the device with them and is bound by the
-// matrix cores (the 64-instance sweep's lockstep matvec 286 / 333 us).  Launches of
+// Squaring (colpower.hpp) or stepping: the step count from which a single matvec by
+// squaring is the faster one, by the tiles of the longest chain and the direction (the
+// transposed stepper is the faster stepper).  Squaring also pays per set bit of the count,
+// so the line lies where counts of many bits break even.  Stepping / squaring in us, FP64
+// forward: 64^2 (1 tile) 16 steps 5.3 / 5.0, 31 steps 7.1 / 6.6; 128^2 (2) 31 steps 7.1 / 8.0,
+// 34 steps 7.5 / 7.0, 200 steps 30.3 / 8.9; 256^2 (3) 63 steps 11.6 / 13.5, 76 steps 13.3 /
+// 13.1, 200 steps 30.4 / 15.3; 384^2 (4) 176 steps 27.3 / 26.3, 200 steps 30.6 / 27.3; 512^2
+// (6) 127 steps 54.7 / 59.2, 140 steps 59.8 / 58.9, 200 steps 84.8 / 64.5.  FP64 adjoint: 1
+// tile 22 steps 5.2 / 5.7, 2 tiles 34 steps 6.9 / 6.9, 3 tiles 76 steps 12.8 / 13.1, 6 tiles
+// 159 steps 61.3 / 62.3.  FP32 forward: 1 tile 22 steps 5.2 / 5.9, 2 tiles 31 steps 6.2 / 6.8,
+// 3 tiles 63 steps 9.5 / 10.5, 6 tiles 76 steps 22.8 / 22.4; adjoint: 1 tile 31 steps 5.4 / 5.9,
+// 2 tiles 47 steps 7.0 / 7.0, 3 tiles 70 steps 9.6 / 10.0.  FP32 chains of 4 tiles step: 384^2
+// alone would gain (24.0 / 19.3), but a batch fills the device with them and is bound by
+// the matrix cores (the 64-instance sweep's lockstep matvec 286 / 333 us).  Launches of
 // more than 768 workgroups (profiles of 6 and more periods on the largest grids)
 // queue for compute units and step.  The rule looks at the operator alone, so a
 // batch gives the bits of single runs.
-inline bool power_pays(int M, int nh, int nsteps, bool fp32) {
-    constexpr int kMin64[kPowMaxTiles] = {16, 28, 72, 176, 120, 120};
+inline bool power_pays(int M, int nh, int nsteps, bool fp32, bool adj) {
     constexpr int kNever = 1 << 30;
-    constexpr int kMin32[kPowMaxTiles] = {16, 24, 56, kNever, 80, 80};
+    constexpr int kMin[2][2][kPowMaxTiles] = {
+        {{16, 32, 76, 176, 140, 140}, {32, 34, 80, 192, 160, 160}},    // FP64: forward, adjoint
+        {{24, 32, 64, kNever, 80, 80}, {32, 48, 72, kNever, 80, 80}},  // FP32
+    };
     const int tiles = power_tiles(M, nh);
-    return tiles <= kPowMaxTiles && power_blocks(M, nh) <= 768 && nsteps >= (fp32 ? kMin32 : kMin64)[tiles - 1];
+    return tiles <= kPowMaxTiles && power_blocks(M, nh) <= 768 && nsteps >= kMin[fp32][adj][tiles - 1];
 }
 
 // Squaring (colmatrix.hpp) or the column stepper, for a profile of harmonics up to h.
@@ -729,7 +735,7 @@ struct KolmoOp final : Operator {
     bool use_couple() const { return !gen && couple && force_cols == 0; }
     bool use_bloch() const { return !gen && bloch && (force_cols == 3 || (force_cols == 0 && !couple)); }
 
-    bool use_power() const { return use_couple() && power_pays(M, nh, nsteps, prec == TSK_FP32); }
+    bool use_power(bool adj) const { return use_couple() && power_pays(M, nh, nsteps, prec == TSK_FP32, adj); }
 
     template <typename real> void launch_bloch(const void* x, void* y) const {
         launch_bloch_stepper<real>(N, inst<real>(x, 0, y, nullptr), nullptr, nullptr, 1, 0, tw.as<cplx<real>>(),
@@ -765,7 +771,7 @@ struct KolmoOp final : Operator {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply: input and output must not alias");
         if (gen) return gen2d_apply(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square && use_power()) {
+        if (square && use_power(false)) {
             tuned_wpw = 4;
             if (prec == TSK_FP32)
                 return launch_power<float, false>(inst<float>(x, 0, y, nullptr), stream);
@@ -828,7 +834,7 @@ struct KolmoOp final : Operator {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply_adjoint: input and output must not alias");
         if (gen) return gen2d_apply_adjoint(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square && use_power()) {
+        if (square && use_power(true)) {
             if (prec == TSK_FP32)
                 return launch_power<float, true>(inst<float>(x, 0, y, nullptr), stream);
             return launch_power<double, true>(inst<double>(x, 0, y, nullptr), stream);
@@ -1268,13 +1274,13 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
             if ((kc && c->couple) ||
                 (!kc && !c->couple && c->N == ko[i]->N && c->prop == ko[i]->prop && c->bloch == kb)) {
                 g = c;
-                if (!(kc && ko[i]->use_power())) gids[q].push_back(i);
+                if (!(kc && ko[i]->use_power(false))) gids[q].push_back(i);
             }
         }
         if (!g) {
             b->groups.push_back(std::make_unique<KolmoBatch::Group>());
             gids.push_back({});
-            if (!(kc && ko[i]->use_power())) gids.back().push_back(i);
+            if (!(kc && ko[i]->use_power(false))) gids.back().push_back(i);
             g = b->groups.back().get();
             g->N = ko[i]->N;
             g->prop = ko[i]->prop;
@@ -1284,7 +1290,7 @@ tsk_status kolmo_batch_plan(Operator* const* ops, int count, const KryDesc* Dh, 
             g->force = ko[i]->force_cols;
         }
         g->columns += ko[i]->M + 1;
-        if (kc && ko[i]->use_power()) {
+        if (kc && ko[i]->use_power(false)) {
             pids.push_back(i);
             g->pblocks = std::max(g->pblocks, power_blocks(ko[i]->M, ko[i]->nh));
             g->ptiles = std::max(g->ptiles, power_tiles(ko[i]->M, ko[i]->nh));

@@ -16,7 +16,7 @@ DT = 0.005
 # chains per column nh and their longest length: 96/4: 16 (one full tile), 64/2: 22, 128/5: 17
 # (one mode beyond a tile), 192/4: 32 (two full tiles), 128/3: 29 (odd nh: no chain is its own
 # mirror image but c = 0), 256/4: 43, 384/4: 64, 256/2: 86, 128/1: 85 (a single chain), 512/4: 86.
-# Step counts: the smallest that squares, powers of two and their neighbours.
+# Step counts: near the smallest that square (both sides of the rule), powers of two and their neighbours.
 # Bars: those of the stepper, 1e-11 (FP64) and 2e-5 (FP32) of max |M w|.
 @pytest.mark.parametrize("N,nh,steps,prec,shift,adj", [
     (16, 4, 16, 0, 0.0, False), (96, 4, 31, 0, 0.0, False), (64, 2, 64, 0, 0.3, False), (128, 5, 33, 0, 0.0, True),
