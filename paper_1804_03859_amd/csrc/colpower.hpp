@@ -8,20 +8,27 @@
 // n x n matrix, which run on the matrix cores, and one matrix-vector product
 // per set bit:
 //     for the bits of nsteps from the lowest: if set, x <- x + D x;  D <- 2 D + D D.
-// D, not S, is squared: (I + D)^2 - I = 2 D + D D keeps the relative accuracy of
-// the small step matrix, so the result is closer to the exact power than the
-// nsteps rounded steps are (relative error against long double at 128^2, T = 1:
-// 2e-16 instead of 6e-15 in FP64, 1.3e-7 instead of 2.7e-6 in FP32).  Nothing is
-// kept between calls: every call forms D from the parameters.
+// Where a mode is still near 1, D, not S, is squared: (I + D)^2 - I = 2 D + D D keeps
+// the relative accuracy of the small step matrix.  A mode damped to s < 1/2 would
+// lose its own in D = s - 1, so its diagonal entry turns to s there: the matrix that
+// is kept is C = S - diag(b), b = 1 or 0 by the row, and the recursion
+//     x <- b x + C x;  C_ij <- (b_i + b_j) C_ij + (C C)_ij.
+// The result is closer to the exact power than the nsteps rounded steps are, in the
+// norm (relative error against long double at 128^2, T = 1: 2e-16 instead of 6e-15 in
+// FP64, 1.3e-7 instead of 2.7e-6 in FP32) and mode by mode (worst error in units of
+// eps max_k |S^(n-k)| |S^k| |x|, 200 steps of a chain at 128^2, 256^2, Re = 20: 12 to 15
+// stepped, 2 to 3 here; with b = 1 throughout 3e4 and more, and no digit of a column
+// damped below eps).  Nothing is kept between calls: every call forms C from the
+// parameters.
 //
 // Chains c and nh - c of a column hold the modes ky and -ky; with u_i = (-1)^i
 // s_{len-1-i} the second obeys the first's equations, so one workgroup squares
 // one matrix for both and applies it to four real vectors.
 //
-// Layout.  A workgroup holds D in LDS, row pitch NP + 4 (the fragment reads of 16
+// Layout.  A workgroup holds C in LDS, row pitch NP + 4 (the fragment reads of 16
 // rows x 4 columns then touch each bank equally often), and squares it in place:
 // the C tiles of 16 x 16 are accumulated in registers by
-// v_mfma_{f64,f32}_16x16x4 starting from 2 D and written after a barrier.  One
+// v_mfma_{f64,f32}_16x16x4 starting from (b_i + b_j) C and written after a barrier.  One
 // wavefront owns a row of tiles, so an A fragment is read once for the whole
 // row; chains of two tiles take four wavefronts of one tile (the shortest
 // dependent chain), chains of one tile a single wavefront and no barrier.  S has
@@ -61,7 +68,7 @@ __host__ __device__ inline int power_blocks(int M, int nh) { return 1 + M * (nh 
 __host__ __device__ inline int power_tiles(int M, int nh) { return ((2 * M + 1 + nh - 1) / nh + 15) / 16; }
 template <typename real, int TC> constexpr int power_lds_bytes() {
     constexpr int NP = 16 * TC;
-    return int(sizeof(real)) * (NP * (NP + 4) + 2 * NP * 4) + 8 * 3 * (NP + 8);
+    return int(sizeof(real)) * (NP * (NP + 4) + 2 * NP * 4 + NP) + 8 * 4 * (NP + 8);
 }
 
 // Squarings k before the matrix D of 2^k steps is applied nsteps >> k times: one
@@ -101,10 +108,12 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
         return;
     }
     double* sG = reinterpret_cast<double*>(lds_power);  // factors of the modes, 4 zeros at either end
-    double* sE = sG + (NP + 8);                         // Eh - 1
-    double* sF = sE + (NP + 8);                         // E1 - 1
+    double* sE = sG + (NP + 8);                         // Eh
+    double* s1 = sE + (NP + 8);                         // E1
+    double* sF = s1 + (NP + 8);                         // E1 - b
     real* D = reinterpret_cast<real*>(sF + (NP + 8));
-    real* vec = D + NP * P;  // [2][NP][4]
+    real* vec = D + NP * P;       // [2][NP][4]
+    real* sB = vec + 2 * NP * 4;  // b
     const int pr = nh / 2 + 1, kx = 1 + (slot - 1) / pr, c = (slot - 1) % pr;
     const double kxv = alpha * kx;
     const int jy0 = -M + ((c + M) % nh), len = (M - jy0) / nh + 1;
@@ -116,16 +125,23 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
 
     for (int i = tid; i < NP + 8; i += NT) {
         const int t = i - 4;
-        double g = 0.0, eh = -1.0, e1 = -1.0;
+        double g = 0.0, eh = 0.0, e1 = 0.0, e1b = 0.0;
+        bool near1 = true;
         if (t >= 0 && t < len) {
             const double jy = jy0 + nh * t, K2 = kxv * kxv + jy * jy;
             g = 0.5 * I.amp * kxv * (1.0 - I.cprop / K2);
-            eh = expm1(-K2 * (0.5 * dt) / Re);
-            e1 = eh * (2.0 + eh);
+            const double q = -K2 * (0.5 * dt) / Re, ehm = expm1(q);
+            eh = ehm > -0.5 ? 1.0 + ehm : exp(q);
+            const double e1m = ehm * (2.0 + ehm);
+            near1 = e1m > -0.5;
+            e1 = near1 ? 1.0 + e1m : eh * eh;
+            e1b = near1 ? e1m : e1;
         }
         sG[i] = g;
         sE[i] = eh;
-        sF[i] = e1;
+        s1[i] = e1;
+        sF[i] = e1b;
+        if (t >= 0 && t < NP) sB[t] = near1 ? real(1) : real(0);
     }
     for (int i = tid; i < NP * P; i += NT) D[i] = real(0);
     // columns of the vector block: (re, im) of the chain, (re, im) of the mirrored one
@@ -150,13 +166,13 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
     }
     __syncthreads();
     if (tid < len) {
-        // column tid of D: the RK4 step of a unit vector, nonzero at offsets -4..4
+        // column tid of C: the RK4 step of a unit vector, nonzero at offsets -4..4
         double g[11], eh[9], e1[9];
 #pragma unroll
         for (int o = 0; o < 9; ++o) {
             g[o + 1] = sG[tid + o];
-            eh[o] = 1.0 + sE[tid + o];
-            e1[o] = 1.0 + sF[tid + o];
+            eh[o] = sE[tid + o];
+            e1[o] = s1[tid + o];
         }
         g[0] = g[10] = 0.0;
         double s[11], k1[9], sum[9];
@@ -201,8 +217,9 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
     int cur = 0, bw = 4;
     unsigned e = unsigned(I.nsteps);
     for (int left = power_squarings<TC>(I.nsteps); left > 0; --left) {
-        if (e & 1u) {  // x <- x + D x, PR threads per row
+        if (e & 1u) {  // x <- b x + C x, PR threads per row
             const real* vc = vec + cur * NP * 4;
+            const real b = row < NP ? sB[row] : real(0);
             real a[4] = {real(0), real(0), real(0), real(0)};
             if (row < len) {
                 const int lo = row > bw ? (row - bw) / PR * PR : 0, hi = row + bw + 1 < len ? row + bw + 1 : len;
@@ -220,10 +237,20 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
             }
             if (sgm == 0 && row < NP)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) vec[(cur ^ 1) * NP * 4 + row * 4 + q] = vc[row * 4 + q] + a[q];
+                for (int q = 0; q < 4; ++q)
+                    vec[(cur ^ 1) * NP * 4 + row * 4 + q] = fma(b, vc[row * 4 + q], a[q]);
             cur ^= 1;
         }
         e >>= 1;
+        // b of the rows of the tiles; of the lane's diagonal entry b and whether it turns from
+        // s - 1 to s (judged by the square it is about to become, so off the products' path)
+        real br[4], one[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) br[r] = sB[16 * ti + T::row(lane, r)];
+        const real bd = sB[16 * ti + (lane & 15)], sd = real(1) + D[(16 * ti + (lane & 15)) * (P + 1)];
+        const bool turn = bd != real(0) && sd * sd < real(0.5);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) one[r] = turn && T::row(lane, r) == (lane & 15) ? real(1) : real(0);
         if (TC >= 4 && bw <= 16) {
             // C tiles ti - 2 .. ti + 2 from A and B tiles next to the diagonal; tiles
             // outside the matrix are read clamped, A as zero, and not written
@@ -231,8 +258,10 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
 #pragma unroll
             for (int d = 0; d < 5; ++d) {
                 const int tj = clamp_tile<TC>(ti + d - 2);
+                const real bc = sB[16 * tj + (lane & 15)];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[d][r] = real(2) * pc[T::row(lane, r) * P + 16 * tj];
+                for (int r = 0; r < 4; ++r)
+                    acc[d][r] = fma(br[r] + bc, pc[T::row(lane, r) * P + 16 * tj], d == 2 ? one[r] : real(0));
             }
 #pragma unroll
             for (int dk = -1; dk <= 1; ++dk) {
@@ -259,9 +288,13 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
         } else {
             V acc[NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j) {
+                const real bc = sB[16 * (tj0 + j) + (lane & 15)];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[j][r] = real(2) * pc[T::row(lane, r) * P + 16 * (tj0 + j)];
+                for (int r = 0; r < 4; ++r)
+                    acc[j][r] = fma(br[r] + bc, pc[T::row(lane, r) * P + 16 * (tj0 + j)],
+                                    tj0 + j == ti ? one[r] : real(0));
+            }
 #pragma unroll
             for (int tk = 0; tk < TC; ++tk) {
                 real a[4];
@@ -279,12 +312,14 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) pc[T::row(lane, r) * P + 16 * (tj0 + j)] = acc[j][r];
         }
+        if (turn && lane < 16) sB[16 * ti + lane] = real(0);
         __syncthreads();
         bw = 2 * bw < len ? 2 * bw : len;
     }
-    // the e remaining applications of the last D, its rows in registers
+    // the e remaining applications of the last C, its rows in registers
     constexpr int NR = NP / PR;
     real dr[NR];
+    const real bo = row < NP ? sB[row] : real(0);
 #pragma unroll
     for (int i = 0; i < NR; ++i) dr[i] = row < NP ? D[row * P + sgm + PR * i] : real(0);
     for (; e > 0; --e) {
@@ -303,7 +338,7 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
         cur ^= 1;
         if (sgm == 0 && row < NP)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) vec[cur * NP * 4 + row * 4 + q] = vc[row * 4 + q] + a[q];
+            for (int q = 0; q < 4; ++q) vec[cur * NP * 4 + row * 4 + q] = fma(bo, vc[row * 4 + q], a[q]);
         __syncthreads();
     }
     if (tid < len) {
@@ -320,9 +355,10 @@ __device__ __forceinline__ void couple_power(const ColInst<real>& I, int jstep, 
     }
 }
 
-// One instance.  Grid x: power_blocks.
+// One instance.  Grid x: power_blocks.  (Three wavefronts per SIMD are what the LDS of
+// four and five tiles lets in.)
 template <typename real, int TC, bool ADJ>
-__global__ __launch_bounds__(power_waves(TC) * kWave) void k_couple_power(ColInst<real> I) {
+__global__ __launch_bounds__(power_waves(TC) * kWave, TC == 6 ? 2 : 3) void k_couple_power(ColInst<real> I) {
     extern __shared__ __align__(16) char lds_power[];
     stepper_wave_priority();
     couple_power<real, TC, ADJ>(I, 0, int(blockIdx.x), lds_power);
@@ -332,7 +368,7 @@ __global__ __launch_bounds__(power_waves(TC) * kWave) void k_couple_power(ColIns
 // table as in k_colstep_couple; every instance runs the code of its own tile
 // count (the same arithmetic as alone), the workgroup sized for the largest.
 template <typename real>
-__global__ __launch_bounds__(kPowMaxTiles * kWave) void k_couple_power_batch(const ColInst<real>* __restrict__ insts,
+__global__ __launch_bounds__(kPowMaxTiles * kWave, 4) void k_couple_power_batch(const ColInst<real>* __restrict__ insts,
                                                                              const int* __restrict__ ids, int jstep) {
     extern __shared__ __align__(16) char lds_power[];
     stepper_wave_priority();
