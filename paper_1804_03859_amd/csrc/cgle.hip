@@ -231,10 +231,10 @@ tsk_status launch_cn_levels(int levels, const CnJob& one, const CnJob* jobs, int
 // transposed tables whose result is contiguous in memory.  D = e (S - I) + (e - 1) I
 // keeps the small matrix to full relative accuracy.  A workgroup solves R rows at
 // once, sharing the loads of the multipliers; rows and columns from n to ld are
-// zeroed.  The workgroup after the last rows sets the vectors: propagator v = x,
-// q = 0; resolvent v = 0, q = e A^-1 c1 f.
+// zeroed; b = 1 (cpower.hpp).  The workgroup after the last rows sets the vectors:
+// propagator v = x, q = 0; resolvent v = 0, q = e A^-1 c1 f.
 struct CpowForm {
-    double* D;    // [count][2][ld * ld]
+    double* D;    // [count][cpow_stride]
     double* vec;  // [count][4][ld]
     int ld;
 };
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kCgleMaxN) void k_cgle_form(CnJob one, const CnJob*
         vec[3 * ld + t] = q.y;
         return;
     }
-    double* Dm = f.D + 2 * size_t(ld) * ld * m;
+    double* Dm = f.D + cpow_stride(ld) * m;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = int(blockIdx.x) * R + r;
@@ -322,6 +322,7 @@ __global__ __launch_bounds__(kCgleMaxN) void k_cgle_form(CnJob one, const CnJob*
             x = cmul(e, cconj(cmul(b, d[r])));
             if (t == i) x = cadd(x, em);
         }
+        if (t == i) Dm[2 * size_t(ld) * ld + i] = 1.0;
         Dm[size_t(i) * ld + t] = x.x;
         Dm[size_t(ld) * ld + size_t(i) * ld + t] = x.y;
     }

@@ -7,7 +7,7 @@
 // U^_m, O^_m the N-point DFT coefficients (1/N) sum_l f_l e^{-2 pi i m l / N} of U and
 // dOmega/dy, the index taken mod N (the products that wrap on the grid are the
 // operator's too).  A Lawson RK4 step is a polynomial in A and the diagonal
-// integrating factors: three products form S - I (the STAGE epilogues), then the
+// integrating factors: three products form S - diag(b) (the STAGE epilogues, b as in cpower.hpp), then the
 // powers follow as in cpower.hpp, all columns together.  A profile of harmonics up to h
 // makes A banded (h off the diagonal, 4 h the step), and the products stay inside the
 // band.  The column stepper takes nsteps x 4 dependent stages of three transforms
@@ -19,14 +19,15 @@
 
 namespace tsk {
 
-// A into `A`, its rows scaled by eh into `X`, the diagonal factors into `diag`, the
-// input columns into `vec` (q = 0); the workgroups of matrix index M advance the
-// kx = 0 column.  prof: [N][4] (U^ re, im, O^ re, im).  Grid x: row, grid y: column
+// A into `A`, its rows scaled by eh into `X`, the diagonal factors into `diag`, b of the
+// one-step matrix (cpower.hpp) behind `C`, the input columns into `vec` (q = 0); the
+// workgroups of matrix index M advance the kx = 0 column.  prof: [N][4] (U^ re, im, O^ re, im).  Grid x: row, grid y: column
 // kx - 1 (0 .. M).
 template <typename real>
 __global__ __launch_bounds__(4 * kWave) void k_colmatrix_form(ColInst<real> I, const double* __restrict__ prof, int N,
                                                               int ld, real* __restrict__ A, real* __restrict__ X,
-                                                              double* __restrict__ diag, real* __restrict__ vec) {
+                                                              double* __restrict__ diag, real* __restrict__ vec,
+                                                              real* __restrict__ C) {
     const int M = I.M, NM = 2 * M + 1, row = int(blockIdx.x), m = int(blockIdx.y), tid = int(threadIdx.x);
     if (m == M) {
         for (int q = row * int(blockDim.x) + tid; q < M; q += int(gridDim.x * blockDim.x)) {
@@ -38,11 +39,12 @@ __global__ __launch_bounds__(4 * kWave) void k_colmatrix_form(ColInst<real> I, c
     }
     const double kxv = I.alpha * (m + 1);
     const size_t mat = size_t(ld) * ld;
-    real* Am = A + 2 * mat * m + size_t(row) * ld;
-    real* Xm = X + 2 * mat * m + size_t(row) * ld;
+    real* Am = A + cpow_stride(ld) * m + size_t(row) * ld;
+    real* Xm = X + cpow_stride(ld) * m + size_t(row) * ld;
     const double ji = row - M, Ki = kxv * kxv + ji * ji;
     const bool kept = row < NM;
-    const double ehm = kept ? expm1(-Ki * (0.5 * I.dt) / I.Re) : -1.0, eh = 1.0 + ehm;
+    const double ehq = -Ki * (0.5 * I.dt) / I.Re, ehm = kept ? expm1(ehq) : -1.0;
+    const double eh = ehm > -0.5 ? 1.0 + ehm : kept ? exp(ehq) : 0.0;
     for (int c = tid; c < ld; c += int(blockDim.x)) {
         double ar = 0.0, ai = 0.0;
         if (kept && c < NM) {
@@ -59,10 +61,11 @@ __global__ __launch_bounds__(4 * kWave) void k_colmatrix_form(ColInst<real> I, c
     }
     if (tid == 0) {
         double* dg = diag + size_t(3 * ld) * m;
-        const double e1m = ehm * (2.0 + ehm);
-        dg[row] = kept ? 1.0 + e1m : 0.0;
+        const double e1m = ehm * (2.0 + ehm), e1 = e1m > -0.5 ? 1.0 + e1m : eh * eh;
+        dg[row] = kept ? e1 : 0.0;
         dg[ld + row] = kept ? eh : 0.0;
-        dg[2 * ld + row] = kept ? e1m : 0.0;
+        dg[2 * ld + row] = !kept ? 0.0 : e1m > -0.5 ? e1m : e1;
+        C[cpow_stride(ld) * m + 2 * mat + row] = kept && e1m > -0.5 ? real(1) : real(0);
         real* v = vec + size_t(4 * ld) * m;
         const real* xs = I.xbase + 2ll * M + int64_t(m) * 2 * NM;
         v[row] = kept ? xs[2 * row] : real(0);
@@ -81,7 +84,7 @@ tsk_status colmatrix_run(CpowWork& W, const ColInst<real>& I, const double* prof
     const int ld = W.ld, M = I.M, NM = 2 * M + 1;
     double* diag = W.diag.as<double>();
     hipLaunchKernelGGL(k_colmatrix_form<real>, dim3(ld, M + 1), dim3(4 * kWave), 0, s, I, prof, N, ld, W.D<real>(0),
-                       W.D<real>(1), diag, W.v<real>(0));
+                       W.D<real>(1), diag, W.v<real>(0), W.D<real>(2));
     const int ts = 32 * W.mt, wt = (ld + ts - 1) / ts;
     CpowArgs<real> g{};
     g.A = W.D<real>(0);

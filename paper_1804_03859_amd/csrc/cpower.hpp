@@ -2,16 +2,18 @@
 // matrices.
 //
 // nsteps identical steps v <- S v + h of an n x n complex system (h = 0: a plain
-// propagator) are taken by doubling: with S = I + D,
-//     v <- v + D v + q     (2^k steps, applied for every set bit k of nsteps)
-//     q <- 2 q + D q,  D <- 2 D + D D     (from 2^k to 2^(k+1) steps),
-// q = h at k = 0.  Squaring D instead of S keeps the relative accuracy of the small
-// step matrix.  After `squarings` doublings the last matrix is applied nsteps >>
+// propagator) are taken by doubling: with S = diag(b) + C,
+//     v <- b v + C v + q     (2^k steps, applied for every set bit k of nsteps)
+//     q <- (1 + b) q + C q,  C_ij <- (b_i + b_j) C_ij + (C C)_ij     (to 2^(k+1) steps),
+// q = h at k = 0.  b = 1 where the diagonal entry of S is near 1: C = S - I there, which
+// keeps the relative accuracy of the small step matrix.  Once that entry is below 1/2
+// in modulus, b turns to 0 and C holds S itself: s - 1 would lose a damped mode (as in
+// colpower.hpp).  After `squarings` doublings the last matrix is applied nsteps >>
 // squarings times.
 //
 // Layout: real and imaginary planes, row-major, leading dimension ld (a multiple
-// of 16, or of 32 for two tiles per wavefront), zero beyond n; two buffers that the
-// doublings alternate between.  Vectors: four planes (v re, v im, q re, q im) per
+// of 16, or of 32 for two tiles per wavefront), zero beyond n, and b behind them; two
+// buffers that the doublings alternate between.  Vectors: four planes (v re, v im, q re, q im) per
 // matrix, two buffers.
 //
 // Bands: a matrix whose entries vanish beyond a distance from the diagonal is stored
@@ -42,16 +44,19 @@ namespace tsk {
 
 template <typename real> using vec4 = real __attribute__((ext_vector_type(4)));
 
-// Products G = A B of k_cpow_gemm.  CPOW_SQUARE: out = 2 A + G (B = A).  The other three
-// form D = S - I of a Lawson RK4 step from the advection matrix A (column j's unit
+// Products G = A B of k_cpow_gemm.  CPOW_SQUARE: out = (b_i + b_j) A + G (B = A).  The
+// other three form C of a Lawson RK4 step from the advection matrix A (column j's unit
 // vector through the four stages, diagonal factors e1 = E(h), eh = E(h/2)):
-//     STAGE2: b = A_ij eh_j + h/2 G,  sum = e1_i A_ij + 2 eh_i b,  out = b
-//     STAGE3: b = A_ij eh_j + h/2 G,  sum += 2 eh_i b,             out = eh_i b
-//     STAGE4: b = A_ij e1_j + h G,    out = (e1 - 1) I + h/6 (sum + b)
+//     STAGE2: t = A_ij eh_j + h/2 G,  sum = e1_i A_ij + 2 eh_i t,  out = t
+//     STAGE3: t = A_ij eh_j + h/2 G,  sum += 2 eh_i t,             out = eh_i t
+//     STAGE4: t = A_ij e1_j + h G,    out = (e1 - b) I + h/6 (sum + t)
 enum CpowEpi { CPOW_SQUARE = 0, CPOW_STAGE2, CPOW_STAGE3, CPOW_STAGE4 };
 
+// Reals of a matrix: two planes, and b behind them.
+__host__ __device__ inline size_t cpow_stride(int ld) { return 2 * size_t(ld) * ld + ld; }
+
 template <typename real> struct CpowArgs {
-    const real* A;   // [count][2][ld * ld]
+    const real* A;   // [count][cpow_stride]
     const real* B;
     real* out;
     const real* vin;  // [count][4][ld]
@@ -63,9 +68,9 @@ template <typename real> struct CpowArgs {
     int bit, affine;  // vector updates of this doubling
     // stages only
     real* sum;
-    const double* diag;  // [count][3][ld]: e1, eh, e1 - 1
+    const double* diag;  // [count][3][ld]: e1, eh, e1 - b
     double h;
-    int adj;  // STAGE4: the conjugate transpose of D
+    int adj;  // STAGE4: the conjugate transpose of C
 };
 
 // One row of the vector updates by one wavefront.
@@ -76,6 +81,7 @@ __device__ inline void cpow_row(const real* __restrict__ D, int ld, int ts, int 
     const real* dr = D + size_t(row) * ld;
     const real* di = dr + size_t(ld) * ld;
     real s[4] = {real(0), real(0), real(0), real(0)};
+    const real v0 = vin[row], v1 = vin[ld + row], b = D[2 * size_t(ld) * ld + row];  // under the sum's latency
     const int lo = max(0, ts * (row / ts - band)), hi = min(ld, ts * (row / ts + band + 1));
     for (int k = lo + lane; k < hi; k += kWave) {
         const real a = dr[k], b = di[k];
@@ -101,12 +107,11 @@ __device__ inline void cpow_row(const real* __restrict__ D, int ld, int ts, int 
             s[q] += xor_lane<1>(s[q], lane);
         }
     }
-    const real v0 = vin[row], v1 = vin[ld + row];
     const real q0 = affine ? vin[2 * ld + row] : real(0), q1 = affine ? vin[3 * ld + row] : real(0);
-    v[0] = bit ? v0 + s[0] + q0 : v0;
-    v[1] = bit ? v1 + s[1] + q1 : v1;
-    v[2] = real(2) * q0 + s[2];
-    v[3] = real(2) * q1 + s[3];
+    v[0] = bit ? fma(b, v0, s[0]) + q0 : v0;
+    v[1] = bit ? fma(b, v1, s[1]) + q1 : v1;
+    v[2] = fma(real(1) + b, q0, s[2]);
+    v[3] = fma(real(1) + b, q1, s[3]);
 }
 
 // Workgroup id -> (matrix, workgroup of the matrix): workgroups go to the 8 XCDs
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
     else
         cpow_place(int(blockIdx.x), g.tile_blocks, g.count, m, w);
     const size_t mat = size_t(ld) * ld;
-    const real* A = g.A + 2 * mat * m;
+    const real* A = g.A + cpow_stride(ld) * m;
     if (rows) {
         const int row = 4 * w + wv;
         real v[4];
@@ -156,8 +161,8 @@ __global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
         }
         return;
     }
-    const real* B = g.B + 2 * mat * m;
-    real* O = g.out + 2 * mat * m;
+    const real* B = g.B + cpow_stride(ld) * m;
+    real* O = g.out + cpow_stride(ld) * m;
     constexpr int TS = 16 * MT;
     const int wt = (ld + 2 * TS - 1) / (2 * TS);
     const int r0 = (2 * (w / wt) + (wv >> 1)) * TS, c0 = (2 * (w % wt) + (wv & 1)) * TS;
@@ -175,21 +180,12 @@ __global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
     const real* pa = A + size_t(r0) * ld;
     const real* pb = B + c0;
     V accr[MT][MT], acci[MT][MT];
-    const bool inside = off <= g.band_a;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < MT; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if constexpr (EPI == CPOW_SQUARE) {
-                    const size_t o = size_t(r0 + 16 * i + T::row(lane, r)) * ld + c0 + 16 * j + lr;
-                    accr[i][j][r] = inside ? real(2) * A[o] : real(0);
-                    acci[i][j][r] = inside ? real(2) * A[o + mat] : real(0);
-                } else {
-                    accr[i][j][r] = acci[i][j][r] = real(0);
-                }
-            }
+            for (int r = 0; r < 4; ++r) accr[i][j][r] = acci[i][j][r] = real(0);
     // ST stages of 16 k in registers: while one multiplies, the next ST - 1 load
     constexpr int ST = MT == 1 ? 4 : 2;
     vec4<real> ar[ST][MT], ai[ST][MT];
@@ -237,9 +233,56 @@ __global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
             products(st);
         }
     }
+    // CPOW_SQUARE's (b_i + b_j) A, loaded under the last products and added to their sum:
+    // products added to it one after the other would each be rounded at its size (256
+    // nodes, 9000 steps: error against long double 3e-13, so 1e-13).  Every wavefront
+    // loads the values that only some use (blocks outside the band, the diagonal) and
+    // selects: a branch would wait for each load in turn.
+    constexpr int SQ = EPI == CPOW_SQUARE ? MT : 1;
+    real cx[SQ][SQ][4], cy[SQ][SQ][4], rb[SQ][4], cb[SQ], dx[SQ], dy[SQ];
+    if constexpr (EPI == CPOW_SQUARE) {
+        const real* bm = A + 2 * mat;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int ri = r0 + 16 * i + lr;
+            cb[i] = bm[c0 + 16 * i + lr];
+            dx[i] = A[size_t(ri) * ld + ri];
+            dy[i] = A[size_t(ri) * ld + ri + mat];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) rb[i][r] = bm[r0 + 16 * i + T::row(lane, r)];
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const size_t o = size_t(r0 + 16 * i + T::row(lane, r)) * ld + c0 + 16 * j + lr;
+                    cx[i][j][r] = A[o];
+                    cy[i][j][r] = A[o + mat];
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int st = 0; st < ST - 1; ++st)  // the last ld / 16 mod ST stages, already loaded
         if (k0 + 16 * st < kend) products(st);
+    if constexpr (EPI == CPOW_SQUARE) {
+        const bool inside = off <= g.band_a;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            // the diagonal: b of the square, judged by the square of the entry (cb is b there)
+            const real x = real(1) + dx[i], y = dy[i];
+            const bool turn = off == 0 && cb[i] != real(0) && x * x + y * y < real(0.5);
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const real b = rb[i][r] + cb[j];
+                    const real one = i == j && turn && T::row(lane, r) == lr ? real(1) : real(0);
+                    accr[i][j][r] += inside ? fma(b, cx[i][j][r], one) : real(0);
+                    acci[i][j][r] += inside ? b * cy[i][j][r] : real(0);
+                }
+            if (off == 0 && lane < 16) O[2 * mat + r0 + 16 * i + lr] = turn ? real(0) : cb[i];
+        }
+    }
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -255,7 +298,7 @@ __global__ __launch_bounds__(4 * kWave, 2) void k_cpow_gemm(CpowArgs<real> g) {
                     const double* dg = g.diag + size_t(3 * ld) * m;
                     const double ej = EPI == CPOW_STAGE4 ? dg[cj] : dg[ld + cj];
                     const double hc = EPI == CPOW_STAGE4 ? g.h : 0.5 * g.h, e1i = dg[ri], ehi = dg[ld + ri];
-                    real* sm = g.sum + 2 * mat * m;
+                    real* sm = g.sum + cpow_stride(ld) * m;
                     const double ax = A[o], ay = A[o + mat];
                     const double bx = ax * ej + hc * double(accr[i][j][r]), by = ay * ej + hc * double(acci[i][j][r]);
                     if constexpr (EPI == CPOW_STAGE2) {
@@ -289,7 +332,7 @@ template <typename real> struct CpowOut {
     int n;
 };
 
-// v <- v + D v + q; last: to the caller's output instead of vout.
+// v <- b v + C v + q; last: to the caller's output instead of vout.
 template <typename real>
 __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, CpowOut<real> out, int last) {
     const int ld = g.ld, wv = int(threadIdx.x) / kWave, lane = int(threadIdx.x) % kWave;
@@ -298,7 +341,7 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
     const int row = 4 * w + wv;
     const real* vin = g.vin + size_t(4 * ld) * m;
     real v[4];
-    cpow_row<real>(g.A + 2 * size_t(ld) * ld * m, ld, g.ts, g.band_a, row, vin, true, false, v);
+    cpow_row<real>(g.A + cpow_stride(ld) * m, ld, g.ts, g.band_a, row, vin, true, false, v);
     if (g.affine) {
         v[0] += vin[2 * ld + row];
         v[1] += vin[3 * ld + row];
@@ -322,15 +365,14 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
 }
 
 // Workspace of `count` matrices: diagonal factors (of the stages), two buffers of
-// vectors and nbuf of matrices, the
-// doublings alternating between `first` and `first` ^ 1.
+// vectors and nbuf of matrices, the doublings alternating between `first` and `first` ^ 1.
 struct CpowWork {
     DevBuf mat, vec, diag;
     int count = 0, ld = 0, mt = 1, nbuf = 2, first = 0;
     size_t real_bytes = 8;
     // Bytes per matrix and buffer.
-    static size_t bytes(int ld, size_t rb) { return 2 * size_t(ld) * ld * rb; }
-    template <typename real> real* D(int b) const { return mat.as<real>() + size_t(b) * 2 * ld * ld * count; }
+    static size_t bytes(int ld, size_t rb) { return cpow_stride(ld) * rb; }
+    template <typename real> real* D(int b) const { return mat.as<real>() + size_t(b) * cpow_stride(ld) * count; }
     template <typename real> real* v(int b) const { return vec.as<real>() + size_t(b) * 4 * ld * count; }
     // Leading dimension and tiles per wavefront of `count` n x n matrices: two tiles per
     // wavefront once one each would queue several wavefronts per SIMD (63 matrices of

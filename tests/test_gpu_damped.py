@@ -93,3 +93,86 @@ def test_squared_chains_keep_damped_modes(tsk, N, Re, steps, prec, adj):
                 want = S @ want
             bar = 8 * steps * eps * _majorant(S, xc, steps) + floor
             assert np.all(np.abs(got - want) <= bar), (kx, c, float(np.max(np.abs(got - want) / bar)))
+
+
+def _column_generator(U, d, kx):
+    """Advection matrix of a kx column on the kept modes, from the samples the operator holds."""
+    N = len(U)
+    M = (N - 1) // 3
+    ky = np.arange(-M, M + 1)
+    F = np.exp(-1j * (2 * np.arctan2(LD(0), LD(-1)) / N) *
+               (np.arange(N)[:, None] * np.arange(N)[None, :] % N).astype(LD))
+    u, o = F @ U.astype(LD) / N, F @ d.astype(LD) / N
+    k = LD(0.5) * kx
+    K2 = k * k + LD(1) * ky * ky
+    D = (ky[:, None] - ky[None, :]) % N
+    return 1j * (-u[D] * k + o[D] * k / K2[None, :]), K2
+
+
+# Whole columns (16, 32, 48, 64 and, two tiles per wavefront, 128 modes padded), narrow and full bands.  The column
+# stepper transforms a column at a time, so its bar is one of norms: 8 steps eps max_q |S^(n-q)| |S^q| |x|.
+@pytest.mark.parametrize("N,Re,steps,base,adj,prec", [
+    (16, 0.5, 200, "wide", False, 0), (32, 1.0, 200, "narrow", True, 0), (64, 5.0, 400, "narrow", False, 0),
+    (96, 10.0, 200, "wide", True, 0), (192, 10.0, 200, "narrow", False, 0), (32, 1.0, 200, "wide", False, 1),
+    (192, 20.0, 100, "narrow", True, 1)])
+def test_squared_columns_keep_damped_columns(tsk, N, Re, steps, base, adj, prec):
+    print(f"damped columns N={N} Re={Re} steps={steps} base={base} adj={adj} prec={prec}", flush=True)
+    y = 2 * np.pi * np.arange(N) / N
+    hs = ((1, 0.7), (2, 0.3)) if base == "narrow" else ((1, 0.6), (N // 5, 0.02), (N // 3 + 1, 0.002))
+    U = sum(a * np.sin(h * y + 0.3 * h) for h, a in hs)
+    d = sum(a * h * h * np.sin(h * y + 0.3 * h) for h, a in hs)
+    op = _op(tsk, N, Re, prec, steps)
+    tsk.set_base_parallel(op, U, d)
+    xin, yout = _run(tsk, op, 22, adj)
+    M = (N - 1) // 3
+    eps, floor = (2.0 ** -52, 0.0) if prec == 0 else (2.0 ** -23, 1e-35)
+    norm = lambda v: float(np.linalg.norm(v.astype(complex), 2))  # noqa: E731
+    for kx in sorted({1, M // 2 + 1, M}):
+        A, K2 = _column_generator(U, d, kx)
+        S = _lawson(A, K2, Re)
+        S = S.conj().T if adj else S
+        xc, got = _column(xin, N, kx), _column(yout, N, kx)
+        want, P8 = xc, _power(S, steps // 8)
+        for _ in range(steps):
+            want = S @ want
+        powers = [norm(_power(P8, q)) for q in range(9)]
+        grow = max(powers[q] * powers[8 - q] for q in range(9))
+        bar = 8 * steps * eps * grow * norm(xc) + floor
+        assert norm(got - want) <= bar, (kx, norm(got - want) / bar)
+
+
+# A Ginzburg-Landau propagator below the threshold everywhere (mu0 = -1.5): the state decays by e^(-1.5 T) and more.
+# Bar as above, in the largest norm; the step matrix in extended precision.
+@pytest.mark.parametrize("n,hw,steps,adj", [(16, 20.0, 3000, False), (60, 20.0, 2000, True), (130, 30.0, 2500, False)])
+def test_squared_ginzburg_landau_keeps_decayed_states(tsk, n, hw, steps, adj):
+    print(f"damped cgle n={n} steps={steps} adj={adj}", flush=True)
+    from oracle.cgle import CGLE
+    par = dict(U=2.0, c_u=0.2, c_d=-1.0, mu0=-1.5, mu2=-0.01)
+    ref = CGLE(n=n, half_width=hw, dt=0.01, T=0.01 * steps, **par)
+    op = tsk.create_cgle1d(n, hw)
+    tsk.set_params_cgle(op, par["U"], par["c_u"], par["c_d"], par["mu0"], par["mu2"], 0.01, 0.01 * steps)
+    u = W.cgle_start(n, 5)
+    x = torch.from_numpy(u).cuda()
+    y = torch.zeros_like(x)
+    (tsk.apply_adjoint if adj else tsk.apply)(op, x, y)
+    L = ref.matrix().astype(CLD)
+    L = L.conj().T if adj else L
+    h = LD(0.01) / 2
+    lhs, rhs = np.eye(n) - h * L, np.eye(n) + h * L
+    B = rhs.copy()  # (I - h L)^-1 (I + h L) by elimination (diagonally dominant, tridiagonal)
+    T = lhs.copy()
+    for i in range(1, n):
+        f = T[i, i - 1] / T[i - 1, i - 1]
+        T[i] -= f * T[i - 1]
+        B[i] -= f * B[i - 1]
+    for i in range(n - 1, -1, -1):
+        if i + 1 < n:
+            B[i] -= T[i, i + 1] * B[i + 1]
+        B[i] /= T[i, i]
+    want = u.astype(CLD)
+    for _ in range(steps):
+        want = B @ want
+    bar = 8 * steps * 2.0 ** -52 * np.max(_majorant(B, u.astype(CLD), steps))
+    err = np.max(np.abs(y.cpu().numpy().astype(CLD) - want))
+    assert err <= bar, float(err / bar)
+    assert np.max(np.abs(want)) < 1e-12 * np.max(np.abs(u))
