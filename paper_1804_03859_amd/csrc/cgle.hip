@@ -382,7 +382,6 @@ struct CgleOp final : Operator {
     bool resolvent = false;
     double omega = 0.0, ttrans = 0.0;
     int ntrans = 0;
-    CpowWork pow;  // squaring workspace, sized on first use
 
     const char* name() const override { return "cgle1d"; }
     int64_t physical_reals() const override { return 2 * int64_t(nn); }
@@ -525,9 +524,10 @@ struct CgleOp final : Operator {
         jb.in = static_cast<const double2*>(x);
         jb.out = static_cast<double2*>(y);
         const CnPlan p = cn_plan(jb);
-        if (p.square && pow.ready(nn, 1, sizeof(double), stream)) {
+        CpowWork W;
+        if (p.square && W.place(scratch, stream, nn, 1, sizeof(double), 2, 0)) {
             CpowOut<double> out{reinterpret_cast<double*>(y), 0, nullptr, nn};
-            return cn_square(pow, p, jb, nullptr, 1, 0, threads(), resolvent, out, stream);
+            return cn_square(W, p, jb, nullptr, 1, 0, threads(), resolvent, out, stream);
         }
         return launch_cn_levels(jb.levels, jb, nullptr, 1, 0, threads(), stream);
     }
@@ -608,7 +608,7 @@ struct CgleBatch {
         std::vector<std::unique_ptr<Square>> squares;
     };
     Pass first, second;  // V -> out (or tmp), and (M^H M) tmp -> w
-    CpowWork* work = nullptr;  // of the first operator
+    Operator* lead = nullptr;  // squares in its scratch; null: step
     int n = 0, chunk = 1, threads = 0;
     bool two = false;
 };
@@ -621,7 +621,7 @@ tsk_status cgle_pass_plan(CgleBatch* b, const std::vector<CnJob>& jobs, CgleBatc
     std::vector<CnJob> step;
     std::vector<std::vector<CnJob>> sq;
     for (const CnJob& jb : jobs) {
-        if (!b->work || !cn_plan(jb).square) {
+        if (!b->lead || !cn_plan(jb).square) {
             step.push_back(jb);
             p->levels = std::max(p->levels, jb.levels);
             continue;
@@ -658,9 +658,11 @@ tsk_status cgle_pass_run(CgleBatch* b, const CgleBatch::Pass& p, int j, hipStrea
     for (const auto& g : p.squares)
         for (int c = 0; c < g->count; c += b->chunk) {
             const int cnt = std::min(b->chunk, g->count - c);
-            TSK_TRY(b->work->ensure(b->n, cnt, sizeof(double)));
+            CpowWork W;
+            if (!W.place(b->lead->scratch, s, b->n, cnt, sizeof(double), 2, 0))
+                return fail(TSK_ENOMEM, "no memory for a squared Ginzburg-Landau batch");
             const CpowOut<double> out{nullptr, 0, g->outs.as<double*>() + c, b->n};
-            TSK_TRY(cn_square(*b->work, g->plan, g->first, g->jobs.as<CnJob>() + c, cnt, j, b->threads,
+            TSK_TRY(cn_square(W, g->plan, g->first, g->jobs.as<CnJob>() + c, cnt, j, b->threads,
                               g->first.forced != 0, out, s));
         }
     return TSK_OK;
@@ -699,8 +701,10 @@ tsk_status cgle_batch_plan(Operator* const* ops, int count, const KryDesc* D_hos
     const size_t each = 2 * CpowWork::bytes((c0->nn + 31) / 32 * 32, sizeof(double));
     p->chunk = int(std::min<size_t>(size_t(count), std::max<size_t>(1, (size_t(1) << 30) / each)));
     bool any = false;
-    for (int i = 0; i < count; ++i) any = any || cn_plan(a[i]).square;
-    if (any && c0->pow.ready(c0->nn, p->chunk, sizeof(double), c0->stream)) p->work = &c0->pow;
+    for (int i = 0; i < count; ++i) any = any || cn_plan(a[i]).square || (svd && cn_plan(b[i]).square);
+    // (smaller groups have room in what the largest chunk has)
+    CpowWork W;
+    if (any && W.place(c0->scratch, c0->stream, c0->nn, p->chunk, sizeof(double), 2, 0)) p->lead = c0;
     TSK_TRY(cgle_pass_plan(p.get(), a, &p->first));
     if (svd) TSK_TRY(cgle_pass_plan(p.get(), b, &p->second));
     *out = std::move(p);

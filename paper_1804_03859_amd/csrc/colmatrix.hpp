@@ -79,10 +79,10 @@ inline int band_blocks(int width, int mt) { return (width + 16 * mt - 1) / (16 *
 
 // One matvec (adj: of the transposed propagator) of the instance I, harmonics up to h.
 template <typename real>
-tsk_status colmatrix_run(CpowWork& W, const ColInst<real>& I, const double* prof, int N, int h, bool adj,
+tsk_status colmatrix_run(const CpowWork& W, const ColInst<real>& I, const double* prof, int N, int h, bool adj,
                          int doublings, hipStream_t s) {
     const int ld = W.ld, M = I.M, NM = 2 * M + 1;
-    double* diag = W.diag.as<double>();
+    double* diag = W.diag();
     hipLaunchKernelGGL(k_colmatrix_form<real>, dim3(ld, M + 1), dim3(4 * kWave), 0, s, I, prof, N, ld, W.D<real>(0),
                        W.D<real>(1), diag, W.v<real>(0), W.D<real>(2));
     const int ts = 32 * W.mt, wt = (ld + ts - 1) / ts;

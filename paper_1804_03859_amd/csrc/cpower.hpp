@@ -364,16 +364,22 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
     }
 }
 
-// Workspace of `count` matrices: diagonal factors (of the stages), two buffers of
-// vectors and nbuf of matrices, the doublings alternating between `first` and `first` ^ 1.
+// The arrays of one call on `count` matrices, laid out in scratch memory: nbuf buffers of
+// matrices (the doublings alternate between `first` and `first` ^ 1), two of vectors and
+// the diagonal factors of the stages.
 struct CpowWork {
-    DevBuf mat, vec, diag;
+    char* base = nullptr;
     int count = 0, ld = 0, mt = 1, nbuf = 2, first = 0;
-    size_t real_bytes = 8;
+    size_t rb = 8;
     // Bytes per matrix and buffer.
     static size_t bytes(int ld, size_t rb) { return cpow_stride(ld) * rb; }
-    template <typename real> real* D(int b) const { return mat.as<real>() + size_t(b) * cpow_stride(ld) * count; }
-    template <typename real> real* v(int b) const { return vec.as<real>() + size_t(b) * 4 * ld * count; }
+    template <typename real> real* D(int b) const {
+        return reinterpret_cast<real*>(base) + size_t(b) * cpow_stride(ld) * count;
+    }
+    template <typename real> real* v(int b) const { return D<real>(nbuf) + size_t(b) * 4 * ld * count; }
+    // (behind nbuf strides and 8 ld reals per matrix: a multiple of 16 reals)
+    double* diag() const { return reinterpret_cast<double*>(base + nbuf * bytes(ld, rb) * count + 8 * ld * rb * count); }
+    size_t total() const { return (nbuf * bytes(ld, rb) + 8 * ld * rb + 3 * ld * sizeof(double)) * count; }
     // Leading dimension and tiles per wavefront of `count` n x n matrices: two tiles per
     // wavefront once one each would queue several wavefronts per SIMD (63 matrices of
     // 127: a doubling 26 us with two, 36 with one; 42 of 85: 18 and 14).
@@ -385,29 +391,16 @@ struct CpowWork {
         const int w = 16 * tiles_of(n_, count_);
         return (n_ + w - 1) / w * w;
     }
-    tsk_status ensure(int n_, int count_, size_t rb) {
+    // For launches on `stream`, or false: step instead (Scratch::get).
+    bool place(Scratch& s, hipStream_t stream, int n_, int count_, size_t rb_, int nbuf_, int first_) {
+        count = count_;
         mt = tiles_of(n_, count_);
         ld = ld_of(n_, count_);
-        count = count_;
-        real_bytes = rb;
-        TSK_TRY(mat.ensure(size_t(nbuf) * bytes(ld, rb) * count));
-        TSK_TRY(diag.ensure(3 * size_t(ld) * sizeof(double) * count));
-        return vec.ensure(8 * size_t(ld) * rb * count);
-    }
-    // For a matvec on `stream`, or false: step instead.  A captured matvec steps (its
-    // graph would share the workspace with calls beside its replays, and outlive it);
-    // so does one that finds no memory.  The allocation is legal while another stream
-    // captures.
-    bool ready(int n_, int count_, size_t rb, hipStream_t stream) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-        if (mat.ptr && vec.ptr && ld >= n_ && count == count_ && real_bytes == rb) return true;
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        const bool ok = ensure(n_, count_, rb) == TSK_OK;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (!ok) (void)hipGetLastError();  // the failed allocation is not the stepper's error
-        return ok;
+        rb = rb_;
+        nbuf = nbuf_;
+        first = first_;
+        base = static_cast<char*>(s.get(total(), stream));
+        return base != nullptr;
     }
 };
 

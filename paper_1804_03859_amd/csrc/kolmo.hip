@@ -606,11 +606,9 @@ struct KolmoOp final : Operator {
     int nh = 0;
     double amp = 0.0, y0 = 0.0;
     DevBuf tw, negU, dOdy, Z;
-    // squared columns (colmatrix.hpp): the profiles' DFT coefficients, and the
-    // workspace, sized on first use
+    // squared columns (colmatrix.hpp): the profiles' DFT coefficients
     DevBuf prof;
     int hmax = 0;  // highest harmonic of the profiles
-    CpowWork colpow;
     DevBuf tasks[3];   // single-instance task lists for 1 and 2 columns per wavefront
     int ntasks[3] = {0, 0, 0};
     int force_cols = 0;  // 0: automatic choice; 1, 2: column stepper; 3: Bloch-sector stepper
@@ -742,16 +740,14 @@ struct KolmoOp final : Operator {
                                    stream);
     }
     // Squared columns: base flows that the column stepper would advance, unless a
-    // column variant is forced or there is no workspace.
+    // column variant is forced or there is no memory for W.
     ColumnPlan columns() const { return column_plan(N, M, hmax, nsteps, prec == TSK_FP32); }
-    bool use_columns() {
+    bool use_columns(CpowWork& W) {
         if (gen || couple || bloch || force_cols != 0 || !columns().square) return false;
-        colpow.nbuf = 4;
-        colpow.first = 2;
-        return colpow.ready(2 * M + 1, M, rb(), stream);
+        return W.place(scratch, stream, 2 * M + 1, M, rb(), 4, 2);
     }
-    template <typename real> tsk_status run_columns(const void* x, void* y, bool adj) {
-        return colmatrix_run<real>(colpow, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax,
+    template <typename real> tsk_status run_columns(const CpowWork& W, const void* x, void* y, bool adj) {
+        return colmatrix_run<real>(W, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax,
                                     adj, columns().doublings, stream);
     }
     tsk_status apply(const void* x, void* y) override { return forward(x, y, true); }
@@ -806,8 +802,9 @@ struct KolmoOp final : Operator {
             TSK_HIP(hipGetLastError());
             return TSK_OK;
         }
-        if (square && use_columns())
-            return prec == TSK_FP32 ? run_columns<float>(x, y, false) : run_columns<double>(x, y, false);
+        CpowWork W;
+        if (square && use_columns(W))
+            return prec == TSK_FP32 ? run_columns<float>(W, x, y, false) : run_columns<double>(W, x, y, false);
         auto launch = [&](int c) {
             if (prec == TSK_FP32)
                 dispatch_colstep<float>(N, inst<float>(x, 0, y, nullptr), nullptr, tasks[c].as<ColTask>(), ntasks[c],
@@ -849,8 +846,9 @@ struct KolmoOp final : Operator {
             TSK_HIP(hipGetLastError());
             return TSK_OK;
         }
-        if (square && use_columns())
-            return prec == TSK_FP32 ? run_columns<float>(x, y, true) : run_columns<double>(x, y, true);
+        CpowWork W;
+        if (square && use_columns(W))
+            return prec == TSK_FP32 ? run_columns<float>(W, x, y, true) : run_columns<double>(W, x, y, true);
         if (prec == TSK_FP32)
             dispatch_colstep_adj<float>(N, inst<float>(x, 0, y, nullptr), tasks[1].as<ColTask>(), ntasks[1], prop,
                                         tw.ptr, stream);

@@ -36,6 +36,25 @@ struct DevBuf {
     template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
+// Device memory that holds nothing between calls; a call lays its arrays out in it.
+struct Scratch {
+    DevBuf mem;
+    // `bytes` of it for launches on `stream`, or null: the stream is capturing (a graph
+    // would share the memory with calls beside its replays, and outlive it) or there is no
+    // memory.  The allocation is legal while another stream captures.
+    void* get(size_t bytes, hipStream_t stream) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
+        if (mem.ptr && mem.bytes >= bytes) return mem.ptr;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        const bool ok = mem.ensure(bytes) == TSK_OK;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!ok) (void)hipGetLastError();  // the caller does without: not its error
+        return ok ? mem.ptr : nullptr;
+    }
+};
+
 enum class StateKind { Complex64x2, Real64, Real32 };  // double2 / double / float
 
 struct ArnoldiWork {
@@ -109,6 +128,7 @@ struct Operator {
     double stop_res_floor = -1.0;
     double stop_dup_rel = -1.0;
     ArnoldiWork aw;
+    Scratch scratch;
 
     bool is_complex() const { return kind == StateKind::Complex64x2; }
     int elem_bytes() const { return kind == StateKind::Real32 ? 4 : 8; }
