@@ -525,7 +525,7 @@ struct CgleOp final : Operator {
         jb.out = static_cast<double2*>(y);
         const CnPlan p = cn_plan(jb);
         CpowWork W;
-        if (p.square && W.place(scratch, stream, nn, 1, sizeof(double), 2, 0)) {
+        if (p.square && W.place(scratch(), stream, nn, 1, sizeof(double), 2, 0)) {
             CpowOut<double> out{reinterpret_cast<double*>(y), 0, nullptr, nn};
             return cn_square(W, p, jb, nullptr, 1, 0, threads(), resolvent, out, stream);
         }
@@ -659,7 +659,7 @@ tsk_status cgle_pass_run(CgleBatch* b, const CgleBatch::Pass& p, int j, hipStrea
         for (int c = 0; c < g->count; c += b->chunk) {
             const int cnt = std::min(b->chunk, g->count - c);
             CpowWork W;
-            if (!W.place(b->lead->scratch, s, b->n, cnt, sizeof(double), 2, 0))
+            if (!W.place(b->lead->scratch(), s, b->n, cnt, sizeof(double), 2, 0))
                 return fail(TSK_ENOMEM, "no memory for a squared Ginzburg-Landau batch");
             const CpowOut<double> out{nullptr, 0, g->outs.as<double*>() + c, b->n};
             TSK_TRY(cn_square(W, g->plan, g->first, g->jobs.as<CnJob>() + c, cnt, j, b->threads,
@@ -704,7 +704,7 @@ tsk_status cgle_batch_plan(Operator* const* ops, int count, const KryDesc* D_hos
     for (int i = 0; i < count; ++i) any = any || cn_plan(a[i]).square || (svd && cn_plan(b[i]).square);
     // (smaller groups have room in what the largest chunk has)
     CpowWork W;
-    if (any && W.place(c0->scratch, c0->stream, c0->nn, p->chunk, sizeof(double), 2, 0)) p->lead = c0;
+    if (any && W.place(c0->scratch(), c0->stream, c0->nn, p->chunk, sizeof(double), 2, 0)) p->lead = c0;
     TSK_TRY(cgle_pass_plan(p.get(), a, &p->first));
     if (svd) TSK_TRY(cgle_pass_plan(p.get(), b, &p->second));
     *out = std::move(p);

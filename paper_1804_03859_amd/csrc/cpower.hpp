@@ -364,10 +364,12 @@ __global__ __launch_bounds__(4 * kWave) void k_cpow_apply(CpowArgs<real> g, Cpow
     }
 }
 
-// The arrays of one call on `count` matrices, laid out in scratch memory: nbuf buffers of
+// The arrays of one call on `count` matrices, laid out in scratch memory (held while this
+// lives: until the call has enqueued its launches): nbuf buffers of
 // matrices (the doublings alternate between `first` and `first` ^ 1), two of vectors and
 // the diagonal factors of the stages.
 struct CpowWork {
+    std::unique_lock<std::mutex> lock;
     char* base = nullptr;
     int count = 0, ld = 0, mt = 1, nbuf = 2, first = 0;
     size_t rb = 8;
@@ -393,6 +395,8 @@ struct CpowWork {
     }
     // For launches on `stream`, or false: step instead (Scratch::get).
     bool place(Scratch& s, hipStream_t stream, int n_, int count_, size_t rb_, int nbuf_, int first_) {
+        if (lock.owns_lock()) lock.unlock();
+        lock = std::unique_lock<std::mutex>(s.mu);
         count = count_;
         mt = tiles_of(n_, count_);
         ld = ld_of(n_, count_);
@@ -400,6 +404,7 @@ struct CpowWork {
         nbuf = nbuf_;
         first = first_;
         base = static_cast<char*>(s.get(total(), stream));
+        if (!base) lock.unlock();
         return base != nullptr;
     }
 };

@@ -605,10 +605,14 @@ struct KolmoOp final : Operator {
     bool couple = false;
     int nh = 0;
     double amp = 0.0, y0 = 0.0;
-    DevBuf tw, negU, dOdy, Z;
-    // squared columns (colmatrix.hpp): the profiles' DFT coefficients
+    DevBuf tw, Z;
+    // the base profile: DFT coefficients (FP64, [N][4]; squared columns, colmatrix.hpp), then
+    // -U and dOmega/dy in the operator's precision.  The coefficients and the highest
+    // harmonic (-1: not known yet) are formed with the profile or by the first call that
+    // may square.
     DevBuf prof;
-    int hmax = 0;  // highest harmonic of the profiles
+    std::vector<double> pnu, poy;
+    int hmax = -1;
     DevBuf tasks[3];   // single-instance task lists for 1 and 2 columns per wavefront
     int ntasks[3] = {0, 0, 0};
     int force_cols = 0;  // 0: automatic choice; 1, 2: column stepper; 3: Bloch-sector stepper
@@ -643,15 +647,16 @@ struct KolmoOp final : Operator {
         return TSK_OK;
     }
 
-    // DFT coefficients (1/N) sum_l f_l e^{-2 pi i m l / N} of U = -nu and dOmega/dy = oy
-    tsk_status upload_profile_dft(const std::vector<double>& nu, const std::vector<double>& oy) {
-        std::vector<double> cs(N), sn(N), h(4 * size_t(N)), u(N), o(N);
+    // DFT coefficients (1/N) sum_l f_l e^{-2 pi i m l / N} of U = -pnu and dOmega/dy = poy
+    // into h[N][4], the highest harmonic into hmax
+    void profile_dft(double* h) {
+        std::vector<double> cs(N), sn(N), u(N), o(N);
         const double pi = 3.14159265358979323846264338327950288;
         for (int l = 0; l < N; ++l) {
             cs[l] = std::cos(2.0 * pi * l / N);
             sn[l] = std::sin(2.0 * pi * l / N);
-            u[l] = -nu[l];
-            o[l] = oy[l];
+            u[l] = -pnu[l];
+            o[l] = poy[l];
         }
         for (int m = 0; 2 * m <= N; ++m) {
             double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
@@ -680,8 +685,28 @@ struct KolmoOp final : Operator {
                     hmax = std::max(hmax, std::min(m, N - m));
         // products that wrap on the grid couple the ends of the column
         if (hmax >= N - 2 * M) hmax = 2 * M;
-        TSK_TRY(prof.ensure(h.size() * sizeof(double)));
-        TSK_HIP(hipMemcpy(prof.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
+    }
+    // Whether a profile of one harmonic would square: what does not pay there pays nowhere.
+    bool columns_may_pay() const { return column_plan(N, M, 1, nsteps, prec == TSK_FP32).square; }
+    template <typename real> const real* profile(int field) const {
+        return reinterpret_cast<const real*>(prof.as<double>() + 4 * size_t(N)) + size_t(field) * N;
+    }
+    tsk_status upload_profile() {
+        const size_t coefs = 4 * size_t(N) * sizeof(double);
+        std::vector<char> host(coefs + 2 * size_t(N) * rb());
+        hmax = -1;
+        if (!couple && !bloch && params_set && columns_may_pay()) profile_dft(reinterpret_cast<double*>(host.data()));
+        for (int f = 0; f < 2; ++f)
+            for (int i = 0; i < N; ++i) {
+                const double v = f == 0 ? pnu[i] : poy[i];
+                char* at = host.data() + coefs + (size_t(f) * N + i) * rb();
+                if (prec == TSK_FP32)
+                    *reinterpret_cast<float*>(at) = float(v);
+                else
+                    *reinterpret_cast<double*>(at) = v;
+            }
+        TSK_TRY(prof.ensure(host.size()));
+        TSK_HIP(hipMemcpy(prof.ptr, host.data(), host.size(), hipMemcpyHostToDevice));
         return TSK_OK;
     }
 
@@ -715,8 +740,8 @@ struct KolmoOp final : Operator {
         c.xbase = static_cast<const real*>(xbase);
         c.xstride = xstride;
         c.y = static_cast<real*>(y);
-        c.negU = negU.as<real>();
-        c.dOdy = dOdy.as<real>();
+        c.negU = profile<real>(0);
+        c.dOdy = profile<real>(1);
         c.alpha = alpha;
         c.Re = Re;
         c.dt = dt;
@@ -741,14 +766,28 @@ struct KolmoOp final : Operator {
     }
     // Squared columns: base flows that the column stepper would advance, unless a
     // column variant is forced or there is no memory for W.
-    ColumnPlan columns() const { return column_plan(N, M, hmax, nsteps, prec == TSK_FP32); }
-    bool use_columns(CpowWork& W) {
-        if (gen || couple || bloch || force_cols != 0 || !columns().square) return false;
-        return W.place(scratch, stream, 2 * M + 1, M, rb(), 4, 2);
+    bool use_columns(CpowWork& W, ColumnPlan& p) {
+        if (gen || couple || bloch || force_cols != 0) return false;
+        if (!columns_may_pay()) return false;
+        if (hmax < 0) {  // the parameters came after the profile
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+            std::vector<double> h(4 * size_t(N));
+            profile_dft(h.data());
+            if (hipMemcpyAsync(prof.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, stream) !=
+                    hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
+                (void)hipGetLastError();
+                hmax = -1;
+                return false;
+            }
+        }
+        p = column_plan(N, M, hmax, nsteps, prec == TSK_FP32);
+        return p.square && W.place(scratch(), stream, 2 * M + 1, M, rb(), 4, 2);
     }
-    template <typename real> tsk_status run_columns(const CpowWork& W, const void* x, void* y, bool adj) {
-        return colmatrix_run<real>(W, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax,
-                                    adj, columns().doublings, stream);
+    template <typename real>
+    tsk_status run_columns(const CpowWork& W, const ColumnPlan& p, const void* x, void* y, bool adj) {
+        return colmatrix_run<real>(W, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax, adj, p.doublings,
+                                   stream);
     }
     tsk_status apply(const void* x, void* y) override { return forward(x, y, true); }
     // M^T M x of the singular-value runs, always step by step.  The x-translation
@@ -803,8 +842,9 @@ struct KolmoOp final : Operator {
             return TSK_OK;
         }
         CpowWork W;
-        if (square && use_columns(W))
-            return prec == TSK_FP32 ? run_columns<float>(W, x, y, false) : run_columns<double>(W, x, y, false);
+        ColumnPlan p;
+        if (square && use_columns(W, p))
+            return prec == TSK_FP32 ? run_columns<float>(W, p, x, y, false) : run_columns<double>(W, p, x, y, false);
         auto launch = [&](int c) {
             if (prec == TSK_FP32)
                 dispatch_colstep<float>(N, inst<float>(x, 0, y, nullptr), nullptr, tasks[c].as<ColTask>(), ntasks[c],
@@ -847,8 +887,9 @@ struct KolmoOp final : Operator {
             return TSK_OK;
         }
         CpowWork W;
-        if (square && use_columns(W))
-            return prec == TSK_FP32 ? run_columns<float>(W, x, y, true) : run_columns<double>(W, x, y, true);
+        ColumnPlan p;
+        if (square && use_columns(W, p))
+            return prec == TSK_FP32 ? run_columns<float>(W, p, x, y, true) : run_columns<double>(W, p, x, y, true);
         if (prec == TSK_FP32)
             dispatch_colstep_adj<float>(N, inst<float>(x, 0, y, nullptr), tasks[1].as<ColTask>(), ntasks[1], prop,
                                         tw.ptr, stream);
@@ -1092,9 +1133,9 @@ tsk_status kolmo_set_base_parallel(Operator* op, const double* U, const double* 
             if (std::fabs(k->y0) < 1e-15) k->y0 = 0.0;
         }
     }
-    TSK_TRY(k->upload_real(k->negU, nu));
-    TSK_TRY(k->upload_real(k->dOdy, oy));
-    if (!k->couple && !k->bloch) TSK_TRY(k->upload_profile_dft(nu, oy));
+    k->pnu = nu;
+    k->poy = oy;
+    TSK_TRY(k->upload_profile());
     gen2d_free(k->gen);
     k->gen = nullptr;
     k->base_set = true;

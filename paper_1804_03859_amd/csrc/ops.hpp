@@ -2,12 +2,70 @@
 // device workspace.
 #pragma once
 
+#include <algorithm>
+#include <map>
 #include <memory>
+#include <mutex>
+#include <utility>
 #include <vector>
 
 #include "common.hpp"
 
 namespace tsk {
+
+// Idle device memory of at most kIdleBlocks blocks and kIdleBytes in all (the oldest go
+// first), handed back by Scratch and taken by the next one: hipMalloc of the memory of a
+// squaring integration takes 40 to 110 us, as long as a short integration.  No work uses
+// an idle block any more.  An allocation of the library that fails frees them all and
+// tries again.
+struct IdleMemory {
+    static constexpr size_t kIdleBytes = size_t(128) << 20;
+    static constexpr size_t kIdleBlocks = 8;
+    struct Block {
+        void* ptr;
+        size_t bytes;
+        int device;
+    };
+    std::mutex mu;
+    std::vector<Block> blocks;
+    static IdleMemory& get() {
+        static IdleMemory* const p = new IdleMemory;  // outlives every handle
+        return *p;
+    }
+    bool put(const Block& b) {
+        std::lock_guard<std::mutex> lk(mu);
+        if (b.bytes > kIdleBytes) return false;
+        size_t held = b.bytes;
+        for (const Block& i : blocks) held += i.bytes;
+        while (held > kIdleBytes || blocks.size() >= kIdleBlocks) {
+            held -= blocks.front().bytes;
+            (void)hipFree(blocks.front().ptr);
+            blocks.erase(blocks.begin());
+        }
+        blocks.push_back(b);
+        return true;
+    }
+    // The smallest block of at least `bytes`, or ptr = null.
+    Block take(size_t bytes, int device) {
+        std::lock_guard<std::mutex> lk(mu);
+        size_t best = blocks.size();
+        for (size_t i = 0; i < blocks.size(); ++i)
+            if (blocks[i].device == device && blocks[i].bytes >= bytes &&
+                (best == blocks.size() || blocks[i].bytes < blocks[best].bytes))
+                best = i;
+        if (best == blocks.size()) return Block{nullptr, 0, device};
+        const Block b = blocks[best];
+        blocks.erase(blocks.begin() + std::ptrdiff_t(best));
+        return b;
+    }
+    bool trim() {
+        std::lock_guard<std::mutex> lk(mu);
+        if (blocks.empty()) return false;
+        for (const Block& b : blocks) (void)hipFree(b.ptr);
+        blocks.clear();
+        return true;
+    }
+};
 
 // Device buffer owned by the library (hipMalloc/hipFree), grown on demand.
 struct DevBuf {
@@ -26,7 +84,12 @@ struct DevBuf {
         if (want <= bytes && ptr) return TSK_OK;
         release();
         if (want == 0) want = 16;
-        if (hipMalloc(&ptr, want) != hipSuccess) {
+        hipError_t e = hipMalloc(&ptr, want);
+        if (e != hipSuccess && IdleMemory::get().trim()) {
+            (void)hipGetLastError();
+            e = hipMalloc(&ptr, want);
+        }
+        if (e != hipSuccess) {
             ptr = nullptr;
             return fail(TSK_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed");
         }
@@ -36,22 +99,68 @@ struct DevBuf {
     template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
-// Device memory that holds nothing between calls; a call lays its arrays out in it.
+// Device memory that holds nothing between calls, shared by the operators of one stream: a
+// call lays its arrays out in it and holds `mu` until its last launch is enqueued, so the
+// stream runs one call's use after the other's.  It lives as long as one of the operators.
 struct Scratch {
+    // allocations and synchronisations are legal while another stream captures
+    struct Relaxed {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+        ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    };
+    std::mutex mu;
     DevBuf mem;
-    // `bytes` of it for launches on `stream`, or null: the stream is capturing (a graph
-    // would share the memory with calls beside its replays, and outlive it) or there is no
-    // memory.  The allocation is legal while another stream captures.
+    int device = 0;
+
+    static std::shared_ptr<Scratch> of(hipStream_t stream) {
+        static std::mutex* const mu = new std::mutex;
+        static auto* const live = new std::map<std::pair<int, hipStream_t>, std::weak_ptr<Scratch>>;
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(*mu);
+        for (auto it = live->begin(); it != live->end();) it = it->second.expired() ? live->erase(it) : std::next(it);
+        std::weak_ptr<Scratch>& w = (*live)[{dev, stream}];
+        std::shared_ptr<Scratch> s = w.lock();
+        if (!s) {
+            s = std::make_shared<Scratch>();
+            s->device = dev;
+            w = s;
+        }
+        return s;
+    }
+    ~Scratch() {
+        if (!mem.ptr) return;
+        Relaxed relaxed;
+        int dev = -1;
+        // idle once the device is (the stream may be gone by now)
+        if (hipGetDevice(&dev) == hipSuccess && dev == device && hipDeviceSynchronize() == hipSuccess &&
+            IdleMemory::get().put({mem.ptr, mem.bytes, device})) {
+            mem.ptr = nullptr;
+            mem.bytes = 0;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    // `bytes` of it for launches on `stream` (with mu held), or null: the stream is capturing
+    // (a graph would share the memory with calls beside its replays, and outlive it), it is
+    // each thread's own stream (one handle for several), or there is no memory.
     void* get(size_t bytes, hipStream_t stream) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (stream == hipStreamPerThread) return nullptr;
         if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
         if (mem.ptr && mem.bytes >= bytes) return mem.ptr;
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        const bool ok = mem.ensure(bytes) == TSK_OK;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (!ok) (void)hipGetLastError();  // the caller does without: not its error
-        return ok ? mem.ptr : nullptr;
+        Relaxed relaxed;
+        const IdleMemory::Block b = IdleMemory::get().take(bytes, device);
+        if (b.ptr) {
+            mem.release();
+            mem.ptr = b.ptr;
+            mem.bytes = b.bytes;
+            return mem.ptr;
+        }
+        if (mem.ensure(bytes) == TSK_OK) return mem.ptr;
+        (void)hipGetLastError();  // the caller does without: not its error
+        return nullptr;
     }
 };
 
@@ -128,7 +237,11 @@ struct Operator {
     double stop_res_floor = -1.0;
     double stop_dup_rel = -1.0;
     ArnoldiWork aw;
-    Scratch scratch;
+    std::shared_ptr<Scratch> shared;  // from the first call that needs it
+    Scratch& scratch() {
+        if (!shared) shared = Scratch::of(stream);
+        return *shared;
+    }
 
     bool is_complex() const { return kind == StateKind::Complex64x2; }
     int elem_bytes() const { return kind == StateKind::Real32 ? 4 : 8; }

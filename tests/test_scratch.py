@@ -31,11 +31,13 @@ static hipError_t fake_free(void* p) {
 static hipError_t fake_capturing(hipStream_t, hipStreamCaptureStatus* s) { *s = capturing; return hipSuccess; }
 static hipError_t fake_mode(hipStreamCaptureMode*) { return hipSuccess; }
 static hipError_t fake_sync() { return hipSuccess; }
+static hipError_t fake_device(int* d) { *d = 0; return hipSuccess; }
 #define hipMalloc(p, n) fake_malloc((void**)(p), n)
 #define hipFree fake_free
 #define hipStreamIsCapturing fake_capturing
 #define hipThreadExchangeStreamCaptureMode fake_mode
 #define hipDeviceSynchronize fake_sync
+#define hipGetDevice fake_device
 #include "cpower.hpp"
 namespace tsk {
 tsk_status fail(tsk_status st, const std::string&) { return st; }
@@ -63,6 +65,7 @@ int main() {
     // one matrix, then a batch whose k-th allocation fails, then the batch again: what place() grants has
     // room for all of its arrays, whichever allocation failed before
     for (int k = 0; k < 4; ++k) {
+        IdleMemory::get().trim();
         Scratch s;
         CpowWork w;
         fail_at = -1;
@@ -81,7 +84,57 @@ int main() {
         CHECK(!w.place(s, nullptr, 60, 1, 8, 2, 0));
         capturing = hipStreamCaptureStatusNone;
     }
+    IdleMemory::get().trim();
     CHECK(live.empty());
+    return 0;
+}
+"""
+
+SHARED = r"""
+int main() {
+    auto s1 = reinterpret_cast<hipStream_t>(16), s2 = reinterpret_cast<hipStream_t>(32);
+    {
+        // the operators of one stream share, those of another do not; one call at a time
+        auto a = Scratch::of(s1), b = Scratch::of(s1), c = Scratch::of(s2);
+        CHECK(a == b && a != c);
+        CpowWork w, x, y;
+        CHECK(w.place(*a, s1, 60, 40, 8, 2, 0) && fits<double>(w));
+        CHECK(!b->mu.try_lock());
+        CHECK(y.place(*c, s2, 60, 40, 8, 2, 0) && fits<double>(y) && y.base != w.base);
+        w.lock.unlock();
+        const int before = allocs;
+        CHECK(x.place(*b, s1, 33, 7, 4, 4, 2) && fits<float>(x) && x.base == w.base && allocs == before);
+        CHECK(!Scratch::of(hipStreamPerThread)->get(64, hipStreamPerThread));
+    }
+    // handed back with the last operator, and taken by the next stream's without an allocation
+    CHECK(live.size() == 2);
+    int before = allocs;
+    for (int i = 0; i < 20; ++i) {
+        auto a = Scratch::of(reinterpret_cast<hipStream_t>(64 + 16 * i));
+        CpowWork w;
+        CHECK(w.place(*a, nullptr, 60, 40, 8, 2, 0) && fits<double>(w));
+    }
+    CHECK(allocs == before && live.size() == 2);
+    // bounded: by size, by number
+    {
+        std::vector<std::shared_ptr<Scratch>> many;
+        for (int i = 0; i < 20; ++i) {
+            many.push_back(std::make_shared<Scratch>());
+            CHECK(many.back()->get(1 << 20, s1));
+        }
+        many.push_back(std::make_shared<Scratch>());
+        CHECK(many.back()->get(IdleMemory::kIdleBytes + 1, s1));
+    }
+    size_t held = 0;
+    for (auto& a : live) held += a.second;
+    CHECK(live.size() <= IdleMemory::kIdleBlocks && held <= IdleMemory::kIdleBytes);
+    // an allocation that fails gets the idle memory first
+    DevBuf d;
+    fail_at = allocs;
+    CHECK(d.ensure(1 << 21) == TSK_OK && live.size() == 1);
+    // a block that was never idle is not handed out: growth frees the old one
+    Scratch g;
+    CHECK(g.get(1000, s1) && g.get(5000, s1) && live.size() == 2);
     return 0;
 }
 """
@@ -102,3 +155,7 @@ def _run(tmp_path, body):
 
 def test_layouts_have_room_after_failed_allocations(tmp_path):
     _run(tmp_path, FAILING)
+
+
+def test_operators_of_a_stream_share_and_idle_memory_is_bounded(tmp_path):
+    _run(tmp_path, SHARED)
