@@ -133,7 +133,7 @@ tsk_status tsk_set_base_flow(tsk_op op, const double* U, const double* V,
  * profiles: tsk_apply and tsk_apply_adjoint of many steps square the one-step
  * matrices of whole columns where that is faster (in memory for four matrices per
  * column, allocated on first use and shared by the operators of one stream; captured
- * calls, calls on hipStreamPerThread and calls that find no memory step); otherwise, and in the Arnoldi drivers, the column stepper, whose kx
+ * calls, calls on hipStreamPerThread and calls that find no memory step); otherwise, and in tsk_arnoldi and the batch drivers, the column stepper, whose kx
  * columns per 64-lane wavefront (1 or 2, 2 only for N <= 256) the library times on
  * the first matvec of a given size, precision, base kind and launch size that steps
  * and keeps for the process.  1 or 2 force that column variant (both compute every column with

@@ -337,7 +337,7 @@ tsk_status arnoldi_t(Operator* const* ops, int count, int m, int k, double tol, 
             if (svd) {  // M^dagger M v_j: forward, then adjoint integration
                 TSK_TRY(ops[i]->normal_product(vj, ops[i]->aw.tmp.ptr, Dh[i].w));
             } else {
-                TSK_TRY(ops[i]->apply(vj, Dh[i].w));
+                TSK_TRY(ops[i]->batch_apply(vj, Dh[i].w));
             }
         }
         return TSK_OK;
@@ -638,8 +638,8 @@ tsk_status arnoldi_t(Operator* const* ops, int count, int m, int k, double tol, 
                         for (int q = 0; q < nr2; ++q) {
                             const int i = R[q];
                             if (g < jm[i])
-                                TSK_TRY(ops[i]->apply(static_cast<const TS*>(xb[i]) + size_t(g) * ops[i]->aw.ldv,
-                                                      DR[q].w));
+                                TSK_TRY(ops[i]->batch_apply(
+                                    static_cast<const TS*>(xb[i]) + size_t(g) * ops[i]->aw.ldv, DR[q].w));
                         }
                     }
                     if (timed) TSK_HIP(hipEventRecord(L.ev_apply[2 * g + 1], es));

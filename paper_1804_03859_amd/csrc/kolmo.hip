@@ -789,7 +789,9 @@ struct KolmoOp final : Operator {
         return colmatrix_run<real>(W, inst<real>(x, 0, y, nullptr), prof.as<double>(), N, hmax, adj, p.doublings,
                                    stream);
     }
-    tsk_status apply(const void* x, void* y) override { return forward(x, y, true); }
+    tsk_status apply(const void* x, void* y) override { return forward(x, y, SQUARE_ALL); }
+    // lockstep launches square chains and step columns
+    tsk_status batch_apply(const void* x, void* y) override { return forward(x, y, SQUARE_CHAINS); }
     // M^T M x of the singular-value runs, always step by step.  The x-translation
     // symmetry of a parallel base makes singular values double, and the second
     // copies, which these runs return, enter the Krylov space only through the
@@ -797,16 +799,17 @@ struct KolmoOp final : Operator {
     // applies the same matrix to the real and imaginary parts and rounds a few
     // products, so the copies would come several steps too late to be returned.
     tsk_status normal_product(const void* x, void* mid, void* y) override {
-        TSK_TRY(forward(x, mid, false));
-        return backward(mid, y, false);
+        TSK_TRY(forward(x, mid, SQUARE_NONE));
+        return backward(mid, y, SQUARE_NONE);
     }
-    // square: by repeated squaring, where use_power() (chains) and use_columns()
-    // allow it
-    tsk_status forward(const void* x, void* y, bool square) {
+    // What may be integrated by repeated squaring, where use_power() (chains) and
+    // use_columns() allow it.
+    enum Squaring { SQUARE_NONE, SQUARE_CHAINS, SQUARE_ALL };
+    tsk_status forward(const void* x, void* y, Squaring square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply: input and output must not alias");
         if (gen) return gen2d_apply(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square && use_power(false)) {
+        if (square != SQUARE_NONE && use_power(false)) {
             tuned_wpw = 4;
             if (prec == TSK_FP32)
                 return launch_power<float, false>(inst<float>(x, 0, y, nullptr), stream);
@@ -843,7 +846,7 @@ struct KolmoOp final : Operator {
         }
         CpowWork W;
         ColumnPlan p;
-        if (square && use_columns(W, p))
+        if (square == SQUARE_ALL && use_columns(W, p))
             return prec == TSK_FP32 ? run_columns<float>(W, p, x, y, false) : run_columns<double>(W, p, x, y, false);
         auto launch = [&](int c) {
             if (prec == TSK_FP32)
@@ -866,12 +869,12 @@ struct KolmoOp final : Operator {
     // kept, else one wavefront per workgroup); other parallel bases the
     // transposed column stepper (k_colstep_adj, task list of 1-column tasks);
     // a general 2-D base the transposed pipeline of kolmo2d.hip.
-    tsk_status apply_adjoint(const void* x, void* y) override { return backward(x, y, true); }
-    tsk_status backward(const void* x, void* y, bool square) {
+    tsk_status apply_adjoint(const void* x, void* y) override { return backward(x, y, SQUARE_ALL); }
+    tsk_status backward(const void* x, void* y, Squaring square) {
         if (!ready()) return fail(TSK_ESTATE, "Navier-Stokes parameters or base flow not set");
         if (x == y) return fail(TSK_EINVAL, "apply_adjoint: input and output must not alias");
         if (gen) return gen2d_apply_adjoint(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
-        if (square && use_power(true)) {
+        if (square != SQUARE_NONE && use_power(true)) {
             if (prec == TSK_FP32)
                 return launch_power<float, true>(inst<float>(x, 0, y, nullptr), stream);
             return launch_power<double, true>(inst<double>(x, 0, y, nullptr), stream);
@@ -888,7 +891,7 @@ struct KolmoOp final : Operator {
         }
         CpowWork W;
         ColumnPlan p;
-        if (square && use_columns(W, p))
+        if (square == SQUARE_ALL && use_columns(W, p))
             return prec == TSK_FP32 ? run_columns<float>(W, p, x, y, true) : run_columns<double>(W, p, x, y, true);
         if (prec == TSK_FP32)
             dispatch_colstep_adj<float>(N, inst<float>(x, 0, y, nullptr), tasks[1].as<ColTask>(), ntasks[1], prop,

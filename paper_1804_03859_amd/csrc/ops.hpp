@@ -256,6 +256,9 @@ struct Operator {
         return fail(TSK_EINVAL, std::string("no adjoint propagator for ") + name());
     }
     virtual bool has_adjoint() const { return false; }
+    // M x for an instance of a batch: the arithmetic of a lockstep launch of its kind, so that
+    // an instance gets the same bits in every batch and alone.
+    virtual tsk_status batch_apply(const void* x, void* y) { return apply(x, y); }
     // y = M^dagger M x with mid = M x (a Lanczos step of the singular-value runs)
     virtual tsk_status normal_product(const void* x, void* mid, void* y) {
         TSK_TRY(apply(x, mid));
