@@ -147,7 +147,14 @@ tsk_status tsk_get_tuning(tsk_op op, int* columns_per_wave) {
     })
 }
 
-// Not in the header: lets the tests take the path of a wait that gave up.
+// Not in the header: let the tests take the path of a wait that gave up, and see that it was.
+__attribute__((visibility("default"))) int tskx_flow_gave_up(tsk_op op, int* yes) {
+    TSK_GUARD({
+        TSK_NEED(op);
+        if (!yes) return fail(TSK_EINVAL, "null result");
+        return kolmo_flow_gave_up(op->op.get(), yes);
+    })
+}
 __attribute__((visibility("default"))) int tskx_flow_polls(tsk_op op, int polls) {
     TSK_GUARD({
         TSK_NEED(op);

@@ -12,10 +12,12 @@
 // of the words.
 //
 // Exchange.  A hop carries 32-bit halves of the values in 64-bit words (tag << 32 |
-// bits), written and read whole by relaxed device-scope atomics, the tag numbering
-// the stage.  A consumer polls the words themselves until they carry its tag: one
-// trip through memory, no flags, no fences, and no order between words is assumed.
-// No word is overwritten before it was read: its producer writes the next stage
+// bits), the tag numbering the stage.  They are written and read two at a time by
+// 16-byte buffer accesses of device scope.  What is assumed of these: an aligned
+// 8-byte word is seen whole (a lane's aligned 16 bytes are one request to one cache
+// line); nothing is assumed of the order of words, not even within an access.  A
+// consumer polls the words themselves until they carry its tag: one trip through
+// memory, no flags, no fences.  No word is overwritten before it was read: its producer writes the next stage
 // only after it has received words that its consumers computed from this one.  Tags
 // count on from call to call (a graph replays its own range: the words then hold the
 // last tag of some range, never the first one of this).
@@ -25,6 +27,10 @@
 // work on the GPU) sets `failed` and stops waiting, as do all others then, so that
 // the launch drains; k_flow_repair, launched behind it, computes the integration by
 // one workgroup with plain memory if it finds `failed` set, and clears the words.
+// That takes the 0.1 s of the wait and 13 (64^2) to 62 (256^2) times as long as the stage
+// launches, 3.5 ms a step at 256^2 FP64, so it also notes it in host memory: the
+// operator's later integrations run stage by stage.  So do all on a device whose CUs
+// cannot hold the launch (a partition of the GPU).
 //
 // A complex value is a cell of 4 (FP64) or 2 (FP32) words, moved as one or two quads of
 // 16 bytes (the words of an access need not arrive together).  Layouts (p: row pair,
@@ -51,7 +57,8 @@ template <typename real> struct FlowArgs {
     unsigned long long* toRows;
     unsigned long long* toCols;
     unsigned* failed;
-    unsigned tag;  // of the first stage
+    unsigned* note;  // host memory, set once a launch has given up (or null)
+    unsigned tag;    // of the first stage
     int polls, nsteps;
     double alpha, Re, dt, U0;
 };

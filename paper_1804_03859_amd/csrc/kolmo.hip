@@ -1216,6 +1216,15 @@ tsk_status kolmo_set_flow_polls(Operator* op, int polls) {
     return TSK_OK;
 }
 
+tsk_status kolmo_flow_gave_up(const Operator* op, int* yes) {
+    const auto* k = dynamic_cast<const KolmoOp*>(op);
+    if (!k) return fail(TSK_EINVAL, "not a Navier-Stokes operator");
+    *yes = 0;
+    for (const Gen2D* g : {k->gen, k->nlw})
+        if (g && gen2d_gave_up(g)) *yes = 1;
+    return TSK_OK;
+}
+
 bool kolmo_parallel(const Operator* op) {
     const auto* k = dynamic_cast<const KolmoOp*>(op);
     return k && !k->gen;

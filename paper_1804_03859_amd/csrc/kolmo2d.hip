@@ -31,6 +31,7 @@
 // the products are sqrt(2) times the physical ones; the RHS in packed units is
 // then -rfft2(P')/N^2 with no further sqrt(2).
 #include <cmath>
+#include <mutex>
 #include <vector>
 
 #include "fft.hpp"
@@ -579,15 +580,97 @@ __global__ __launch_bounds__(kGT) void k_flow_repair(FlowArgs<real> g, real* W, 
     }
     for (size_t i = threadIdx.x; i < words; i += kGT) g.toRows[i] = 0;  // toCols follows toRows
     __syncthreads();
-    if (threadIdx.x == 0) *g.failed = 0;
+    if (threadIdx.x == 0) {
+        *g.failed = 0;
+        if (g.note) __hip_atomic_store(g.note, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
+
+// Whether the CUs of the current device hold the whole launch of each kind.
+template <typename real, int N> bool flow_resident() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return false;
+    const void* kernels[3] = {reinterpret_cast<const void*>(&k_flow<real, N, false>),
+                              reinterpret_cast<const void*>(&k_flow<real, N, true>),
+                              reinterpret_cast<const void*>(&k_flow_adj<real, N>)};
+    for (const void* k : kernels) {
+        int per = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kGT, 0) != hipSuccess) return false;
+        if (per * cus < FlowGeo<real, N>::blocks) return false;
+    }
+    return true;
+}
+template <typename real> bool flow_resident(int N) {
+    switch (N) {
+#define X(n) \
+    case n: return flow_resident<real, n>();
+        X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256)
+#undef X
+    }
+    return false;
+}
+
+// A word of pinned host memory that the device can write: one page of them for the
+// process, so that an operator need not allocate its own.
+class FlowNote {
+    static constexpr int kWords = 1024;
+    struct Page {
+        std::mutex mu;
+        unsigned* words = nullptr;
+        bool tried = false, used[kWords] = {};
+    };
+    static Page& page() {
+        static Page* const p = new Page;
+        return *p;
+    }
+    int at = -1;
+
+ public:
+    FlowNote() {
+        Page& p = page();
+        std::lock_guard<std::mutex> lk(p.mu);
+        if (!p.tried) {
+            p.tried = true;
+            if (hipHostMalloc(reinterpret_cast<void**>(&p.words), kWords * sizeof(unsigned),
+                              hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+                (void)hipGetLastError();
+                p.words = nullptr;
+            }
+        }
+        for (int i = 0; p.words && i < kWords && at < 0; ++i)
+            if (!p.used[i]) at = i;
+        if (at >= 0) p.used[at] = true;
+        clear();
+    }
+    FlowNote(const FlowNote&) = delete;
+    ~FlowNote() {
+        if (at < 0) return;
+        std::lock_guard<std::mutex> lk(page().mu);
+        page().used[at] = false;
+    }
+    unsigned* host() const { return at < 0 ? nullptr : page().words + at; }
+    unsigned* device() const {
+        void* d = nullptr;
+        if (at < 0 || hipHostGetDevicePointer(&d, host(), 0) != hipSuccess) return nullptr;
+        return static_cast<unsigned*>(d);
+    }
+    bool set() const { return at >= 0 && __atomic_load_n(host(), __ATOMIC_RELAXED) != 0; }
+    void clear() {
+        if (at >= 0) __atomic_store_n(host(), 0u, __ATOMIC_RELAXED);
+    }
+};
 
 // The exchange of one Gen2D: words of both directions, the failure flag, the state
 // between launches, and the tag of the next stage.
 struct FlowWork {
+    FlowNote note;  // outlives the buffers, whose release waits for the launches
     DevBuf words, mid;
     unsigned tag = 1;
     int polls = kFlowPolls;
+    bool resident = false, noting = true;
+    bool one_launch() const { return resident && !note.set(); }
     static size_t count(int N, bool fp32) { return size_t(5) * (fp32 ? 2 : 4) * ((N - 1) / 3 + 1) * N; }
     tsk_status init(int N, bool fp32, size_t state_bytes) {
         const size_t b = (count(N, fp32) + 1) * sizeof(unsigned long long);
@@ -595,6 +678,7 @@ struct FlowWork {
         TSK_TRY(mid.ensure(state_bytes));
         TSK_HIP(hipMemset(words.ptr, 0, b));
         TSK_HIP(hipStreamSynchronize(nullptr));
+        resident = fp32 ? flow_resident<float>(N) : flow_resident<double>(N);
         return TSK_OK;
     }
 };
@@ -608,6 +692,7 @@ void flow_run(FlowWork& w, FlowArgs<real> g, real* W, real* Acc, cplx<real>* Q, 
     g.toRows = base;
     g.toCols = base + G::words(KIND == FLOW_ADJ ? 1 : 4);
     g.failed = reinterpret_cast<unsigned*>(base + total);
+    g.note = w.noting ? w.note.device() : nullptr;
     g.polls = w.polls;
     const int launches = (nsteps + kFlowSteps - 1) / kFlowSteps;
     const void* in = x;
@@ -635,14 +720,15 @@ void gen_run_adj(FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<
     using C = cplx<real>;
     constexpr int MC = Geo2<N>::MC;
     const C* twc = static_cast<const C*>(tw);
-    if constexpr (flow_fits(N)) {
-        FlowArgs<real> g{};
-        g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
-        g.tw = twc;
-        g.alpha = alpha, g.Re = Re, g.dt = dt;
-        flow_run<real, N, FLOW_ADJ>(fw, g, W, Acc, G1, Q4, x, y, nsteps, s);
-        return;
-    }
+    if constexpr (flow_fits(N))
+        if (fw.one_launch()) {
+            FlowArgs<real> g{};
+            g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
+            g.tw = twc;
+            g.alpha = alpha, g.Re = Re, g.dt = dt;
+            flow_run<real, N, FLOW_ADJ>(fw, g, W, Acc, G1, Q4, x, y, nsteps, s);
+            return;
+        }
     hipLaunchKernelGGL((k_gen_col_adj<real, N>), dim3(MC), dim3(kGT), 0, s, static_cast<const real*>(x), W, Acc, Q4,
                        G1, static_cast<real*>(y), twc, alpha, Re, dt, 0, int(GEN_FIRST));
     for (int st = 0; st < nsteps; ++st)
@@ -679,15 +765,16 @@ void gen_run(FlowWork& fw, const void* x, void* y, real* W, real* Acc, cplx<real
     constexpr int MC = Geo2<N>::MC;
     constexpr int RPW = gen_rows_per_group<real, N>();
     const C* twc = static_cast<const C*>(tw);
-    if constexpr (flow_fits(N) && RM != ROW_FIELDS) {
-        FlowArgs<real> g{};
-        g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
-        g.fvec = fvec;
-        g.tw = twc;
-        g.alpha = alpha, g.Re = Re, g.dt = dt, g.U0 = U0;
-        flow_run<real, N, RM == ROW_NL ? FLOW_NL : FLOW_LIN>(fw, g, W, Acc, Q, Gf, x, y, nsteps, s);
-        return;
-    }
+    if constexpr (flow_fits(N) && RM != ROW_FIELDS)
+        if (fw.one_launch()) {
+            FlowArgs<real> g{};
+            g.U = U, g.V = V, g.Ox = Ox, g.Oy = Oy;
+            g.fvec = fvec;
+            g.tw = twc;
+            g.alpha = alpha, g.Re = Re, g.dt = dt, g.U0 = U0;
+            flow_run<real, N, RM == ROW_NL ? FLOW_NL : FLOW_LIN>(fw, g, W, Acc, Q, Gf, x, y, nsteps, s);
+            return;
+        }
     hipLaunchKernelGGL((k_gen_col<real, N>), dim3(MC), dim3(kGT), 0, s, static_cast<const real*>(x), W, Acc, Q, Gf,
                        static_cast<real*>(y), twc, alpha, Re, dt, 0, int(GEN_FIRST), fvec);
     if constexpr (RM == ROW_FIELDS) {
@@ -759,7 +846,12 @@ tsk_status gen2d_create(int N, bool fp32, const double* U, const double* V, cons
 
 void gen2d_free(Gen2D* g) { delete g; }
 
-void gen2d_set_polls(Gen2D* g, int polls) { g->flow.polls = polls < 0 ? kFlowPolls : polls; }
+void gen2d_set_polls(Gen2D* g, int polls) {
+    g->flow.polls = polls >= 0 ? polls : polls == -1 ? kFlowPolls : 0;
+    g->flow.noting = polls < 0;
+    g->flow.note.clear();
+}
+bool gen2d_gave_up(const Gen2D* g) { return g->flow.note.set(); }
 
 namespace {
 template <int RM>

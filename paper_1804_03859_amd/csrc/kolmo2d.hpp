@@ -13,8 +13,11 @@ struct Gen2D;
 tsk_status gen2d_create(int N, bool fp32, const double* U, const double* V, const double* Ox, const double* Oy,
                         Gen2D** out);
 void gen2d_free(Gen2D* g);
-// Polls before a wait between workgroups gives up (genflow.hpp); negative: the default.
+// Polls before a wait between workgroups gives up (genflow.hpp), unnoted; -1: the default;
+// -2: none, noted.  Clears the note.
 void gen2d_set_polls(Gen2D* g, int polls);
+// Whether a launch has given up and noted it: integrations run stage by stage since.
+bool gen2d_gave_up(const Gen2D* g);
 // One matvec (T/dt = nsteps Lawson RK4 steps) of the packed state x into y.
 // tw: exp(-2 pi i t / N), t < N, in the operator's precision (complex).
 tsk_status gen2d_apply(Gen2D* g, double alpha, double Re, double dt, int nsteps, const void* x, void* y,

@@ -294,8 +294,10 @@ int kolmo_nsteps(const Operator* op);
 // get reports the forced or tuned value (0 = not tuned yet).
 tsk_status kolmo_set_tuning(Operator* op, int cols);
 tsk_status kolmo_get_tuning(const Operator* op, int* cols);
-// Polls before a wait inside a two-dimensional integration gives up; negative: the default.
+// Polls before a wait inside a two-dimensional integration gives up (gen2d_set_polls);
+// whether one has and the operator's integrations run stage by stage since.
 tsk_status kolmo_set_flow_polls(Operator* op, int polls);
+tsk_status kolmo_flow_gave_up(const Operator* op, int* yes);
 // Launch shape of the spectral-coupling stepper: wavefronts per workgroup, 0 =
 // tuned (get: the shape of the last launch, 0 before the first).
 tsk_status kolmo_set_stepper_waves(Operator* op, int w);
