@@ -147,6 +147,14 @@ tsk_status tsk_get_tuning(tsk_op op, int* columns_per_wave) {
     })
 }
 
+// Not in the header: lets the tests step where the library would square.
+__attribute__((visibility("default"))) int tskx_step_only(tsk_op op, int on) {
+    TSK_GUARD({
+        TSK_NEED(op);
+        return kolmo_step_only(op->op.get(), on);
+    })
+}
+
 // Not in the header: let the tests take the path of a wait that gave up, and see that it was.
 __attribute__((visibility("default"))) int tskx_flow_gave_up(tsk_op op, int* yes) {
     TSK_GUARD({

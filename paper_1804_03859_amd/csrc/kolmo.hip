@@ -617,7 +617,9 @@ struct KolmoOp final : Operator {
     int ntasks[3] = {0, 0, 0};
     int force_cols = 0;  // 0: automatic choice; 1, 2: column stepper; 3: Bloch-sector stepper
     int force_wpw = 0;   // coupling stepper's wavefronts per workgroup: 0 tuned, else 1, 2 or 4
-    int tuned_wpw = 0;   // the tuned (or forced) shape of the last launch
+    int tuned_wpw = 0;   // the tuned (or forced) shape of the last forward launch that stepped
+    bool squared_last = false;  // the last forward matvec squared: reported as 4, steers no stepper
+    bool step_only = false;     // no integration squares (tests)
     Gen2D* gen = nullptr;  // general two-dimensional base flow (kolmo2d.hip), else parallel
     // nonlinear forced equation (fixed-point solvers): pipeline workspace, packed
     // forcing and laminar state, drift, and the inputs the forcing is made from
@@ -758,7 +760,9 @@ struct KolmoOp final : Operator {
     bool use_couple() const { return !gen && couple && force_cols == 0; }
     bool use_bloch() const { return !gen && bloch && (force_cols == 3 || (force_cols == 0 && !couple)); }
 
-    bool use_power(bool adj) const { return use_couple() && power_pays(M, nh, nsteps, prec == TSK_FP32, adj); }
+    bool use_power(bool adj) const {
+        return use_couple() && !step_only && power_pays(M, nh, nsteps, prec == TSK_FP32, adj);
+    }
 
     template <typename real> void launch_bloch(const void* x, void* y) const {
         launch_bloch_stepper<real>(N, inst<real>(x, 0, y, nullptr), nullptr, nullptr, 1, 0, tw.as<cplx<real>>(),
@@ -767,7 +771,7 @@ struct KolmoOp final : Operator {
     // Squared columns: base flows that the column stepper would advance, unless a
     // column variant is forced or there is no memory for W.
     bool use_columns(CpowWork& W, ColumnPlan& p) {
-        if (gen || couple || bloch || force_cols != 0) return false;
+        if (gen || couple || bloch || force_cols != 0 || step_only) return false;
         if (!columns_may_pay()) return false;
         if (hmax < 0) {  // the parameters came after the profile
             hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -810,7 +814,7 @@ struct KolmoOp final : Operator {
         if (x == y) return fail(TSK_EINVAL, "apply: input and output must not alias");
         if (gen) return gen2d_apply(gen, alpha, Re, dt, nsteps, x, y, tw.ptr, stream);
         if (square != SQUARE_NONE && use_power(false)) {
-            tuned_wpw = 4;
+            squared_last = true;
             if (prec == TSK_FP32)
                 return launch_power<float, false>(inst<float>(x, 0, y, nullptr), stream);
             return launch_power<double, false>(inst<double>(x, 0, y, nullptr), stream);
@@ -832,6 +836,7 @@ struct KolmoOp final : Operator {
                                       prefer));
             }
             tuned_wpw = w;
+            squared_last = false;
             launch(w);
             TSK_HIP(hipGetLastError());
             return TSK_OK;
@@ -1204,7 +1209,7 @@ tsk_status kolmo_set_stepper_waves(Operator* op, int w) {
 tsk_status kolmo_get_stepper_waves(const Operator* op, int* w) {
     const auto* k = dynamic_cast<const KolmoOp*>(op);
     if (!k) return fail(TSK_EINVAL, "not a Navier-Stokes operator");
-    *w = k->force_wpw ? k->force_wpw : k->tuned_wpw;
+    *w = k->force_wpw ? k->force_wpw : k->squared_last ? 4 : k->tuned_wpw;
     return TSK_OK;
 }
 
@@ -1222,6 +1227,13 @@ tsk_status kolmo_flow_gave_up(const Operator* op, int* yes) {
     *yes = 0;
     for (const Gen2D* g : {k->gen, k->nlw})
         if (g && gen2d_gave_up(g)) *yes = 1;
+    return TSK_OK;
+}
+
+tsk_status kolmo_step_only(Operator* op, int on) {
+    auto* k = dynamic_cast<KolmoOp*>(op);
+    if (!k) return fail(TSK_EINVAL, "not a Navier-Stokes operator");
+    k->step_only = on != 0;
     return TSK_OK;
 }
 

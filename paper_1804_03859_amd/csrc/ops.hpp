@@ -298,6 +298,8 @@ tsk_status kolmo_get_tuning(const Operator* op, int* cols);
 // whether one has and the operator's integrations run stage by stage since.
 tsk_status kolmo_set_flow_polls(Operator* op, int polls);
 tsk_status kolmo_flow_gave_up(const Operator* op, int* yes);
+// No integration of the operator squares.
+tsk_status kolmo_step_only(Operator* op, int on);
 // Launch shape of the spectral-coupling stepper: wavefronts per workgroup, 0 =
 // tuned (get: the shape of the last launch, 0 before the first).
 tsk_status kolmo_set_stepper_waves(Operator* op, int w);
