@@ -541,25 +541,28 @@ inline int couple_slots(int M, int nh) { return ((2 * M + 1 + nh - 1) / nh + kWa
 // Squaring (colpower.hpp) or stepping: the step count from which a single matvec by
 // squaring is the faster one, by the tiles of the longest chain and the direction (the
 // transposed stepper is the faster stepper).  Squaring also pays per set bit of the count,
-// so the line lies where counts of many bits break even.  Stepping / squaring in us, FP64
-// forward: 64^2 (1 tile) 16 steps 5.3 / 5.0, 31 steps 7.1 / 6.6; 128^2 (2) 31 steps 7.1 / 8.0,
-// 34 steps 7.5 / 7.0, 200 steps 30.3 / 8.9; 256^2 (3) 63 steps 11.6 / 13.5, 76 steps 13.3 /
-// 13.1, 200 steps 30.4 / 15.3; 384^2 (4) 176 steps 27.3 / 26.3, 200 steps 30.6 / 27.3; 512^2
-// (6) 127 steps 54.7 / 59.2, 140 steps 59.8 / 58.9, 200 steps 84.8 / 64.5.  FP64 adjoint: 1
-// tile 22 steps 5.2 / 5.7, 2 tiles 34 steps 6.9 / 6.9, 3 tiles 76 steps 12.8 / 13.1, 6 tiles
-// 159 steps 61.3 / 62.3.  FP32 forward: 1 tile 22 steps 5.2 / 5.9, 2 tiles 31 steps 6.2 / 6.8,
-// 3 tiles 63 steps 9.5 / 10.5, 6 tiles 76 steps 22.8 / 22.4; adjoint: 1 tile 31 steps 5.4 / 5.9,
-// 2 tiles 47 steps 7.0 / 7.0, 3 tiles 70 steps 9.6 / 10.0.  FP32 chains of 4 tiles step: 384^2
-// alone would gain (24.0 / 19.3), but a batch fills the device with them and is bound by
-// the matrix cores (the 64-instance sweep's lockstep matvec 286 / 333 us).  Launches of
-// more than 768 workgroups (profiles of 6 and more periods on the largest grids)
-// queue for compute units and step.  The rule looks at the operator alone, so a
-// batch gives the bits of single runs.
+// so the line lies where counts of many bits break even.  Stepping / squaring in us at
+// four chains a column.  FP64 forward: 64^2 (1 tile) 23 steps 6.1 / 6.5, 31 steps 7.1 / 7.0;
+// 128^2 (2) 33 steps 7.4 / 7.4, 47 steps 9.3 / 8.8, 200 steps 30.3 / 9.5; 256^2 (3) 77 steps
+// 13.6 / 14.0, 87 steps 15.0 / 14.3, 200 steps 30.4 / 15.5; 384^2 (4) 177 steps 27.5 / 28.1,
+// 199 steps 30.6 / 28.9; 512^2 (6) 141 steps 60.8 / 62.3, 159 steps 68.1 / 65.1, 200 steps
+// 84.8 / 66.7.  FP64 adjoint: 1 tile 32 steps 6.6 / 5.6, 2 tiles 39 steps 7.6 / 8.3, 47
+// steps 8.7 / 8.8, 3 tiles 81 steps 13.5 / 13.0, 4 tiles 193 steps 29.3 / 27.5, 6 tiles 161
+// steps 62.1 / 62.3.  FP32 forward: 1 tile 31 steps 6.1 / 6.3, 2 tiles 33 steps 6.3 / 6.3, 3
+// tiles 65 steps 9.6 / 9.5, 6 tiles 81 steps 23.4 / 23.5; adjoint: 1 tile 33 steps 5.6 / 5.4,
+// 2 tiles 49 steps 7.3 / 6.8, 3 tiles 73 steps 9.8 / 10.2, 83 steps 10.9 / 10.3, 6 tiles 81
+// steps 24.0 / 23.1.  5 tiles (512^2, five chains: 140 steps FP64 61.9 / 52.5, 80 steps FP32
+// 23.4 / 19.5) take the lines of 6.  FP32 chains of 4 tiles: alone squaring is faster from
+// some 160 steps on (384^2 200 steps 24.0 / 19.3, 256 steps 29.6 / 18.9), but many of them
+// fill the device and are bound by the matrix cores, and the rule looks at the operator
+// alone: a lockstep Arnoldi step of 20 operators at 384^2 takes 325 / 342 at 256 steps, 354
+// / 361 at 300 and 424 / 376 at 400.  Launches of more than 768 workgroups
+// (profiles of 6 and more periods on the largest grids) queue for compute units and step.
+// The rule looks at the operator alone, so a batch gives the bits of single runs.
 inline bool power_pays(int M, int nh, int nsteps, bool fp32, bool adj) {
-    constexpr int kNever = 1 << 30;
     constexpr int kMin[2][2][kPowMaxTiles] = {
-        {{16, 32, 76, 176, 140, 140}, {32, 34, 80, 192, 160, 160}},    // FP64: forward, adjoint
-        {{24, 32, 64, kNever, 80, 80}, {32, 48, 72, kNever, 80, 80}},  // FP32
+        {{28, 32, 80, 184, 146, 146}, {32, 44, 80, 192, 160, 160}},    // FP64: forward, adjoint
+        {{32, 32, 64, 320, 80, 80}, {32, 48, 76, 320, 80, 80}},  // FP32
     };
     const int tiles = power_tiles(M, nh);
     return tiles <= kPowMaxTiles && power_blocks(M, nh) <= 768 && nsteps >= kMin[fp32][adj][tiles - 1];

@@ -5,6 +5,8 @@ import pytest
 import torch
 
 import workloads as W
+from oracle.kolmogorov import Kolmogorov
+from oracle.optimal import kolmo_apply_adjoint
 
 pytestmark = pytest.mark.gpu
 
@@ -23,6 +25,51 @@ def _op(tsk, N, nh, steps, prec, shift=0.0, Re=20.0):
 
 def _step_only(tsk, op, on):
     assert tsk.load().tskx_step_only(op.h, int(on)) == 0
+
+
+# chains of 11 (one tile), 22 (two), 29 of an odd count (two), 43 (three), 64 (four), 69 (five), 85 and 86 modes
+# (six); counts at and just above the line, and odd ones.  Bars: the stepper's, of max |M w|.
+@pytest.mark.parametrize("N,nh,steps,prec,shift,adj", [
+    (64, 4, 31, 0, 0.2, False), (64, 4, 33, 0, 0.0, True), (128, 4, 33, 0, 0.0, False), (128, 3, 47, 0, 0.7, True),
+    (256, 4, 81, 0, 0.0, False), (256, 4, 83, 0, 0.1, True), (384, 4, 185, 0, 0.3, False), (384, 4, 193, 0, 0.0, True),
+    (512, 5, 147, 0, 0.0, False), (512, 5, 161, 0, 0.2, True), (128, 1, 151, 0, 0.2, False), (512, 4, 165, 0, 0.0, True),
+    (64, 4, 33, 1, 0.0, False), (64, 4, 35, 1, 0.2, True), (128, 4, 37, 1, 0.0, False), (128, 4, 51, 1, 0.1, True),
+    (256, 4, 65, 1, 0.4, False), (256, 4, 77, 1, 0.0, True), (384, 4, 321, 1, 0.0, False), (384, 4, 325, 1, 0.2, True),
+    (512, 5, 81, 1, 0.0, False), (512, 5, 83, 1, 0.1, True), (512, 4, 85, 1, 0.0, False), (512, 4, 93, 1, 0.0, True)])
+def test_squared_path_matches_oracle_and_is_taken(tsk, N, nh, steps, prec, shift, adj):
+    print(f"power path N={N} nh={nh} steps={steps} prec={prec} adj={adj}", flush=True)
+    op, U = _op(tsk, N, nh, steps, prec, shift)
+    Ug = np.repeat(U[:, None], N, axis=1)
+    zero = np.zeros_like(Ug)
+    ref = Kolmogorov(N, 0.5, 20.0, DT, steps * DT, Ug, zero, zero, nh * nh * Ug)
+    w = ref.project(W.kolmo_start_physical(N, 11))
+    x, y, z = op.new_state(), op.new_state(), op.new_state()
+    tsk.from_physical(op, torch.from_numpy(w).to("cuda", op.state_dtype).reshape(-1), x)
+    apply = tsk.apply_adjoint if adj else tsk.apply
+    apply(op, x, y)
+    _step_only(tsk, op, True)
+    apply(op, x, z)
+    assert not torch.equal(y, z)
+    want = kolmo_apply_adjoint(ref, w) if adj else ref.apply(w)
+    tol = 1e-11 if prec == 0 else 2e-5
+    for s in (y, z):
+        got = torch.zeros(N * N, dtype=op.state_dtype, device="cuda")
+        tsk.to_physical(op, s, got)
+        assert np.max(np.abs(got.double().cpu().numpy().reshape(N, N) - want)) <= tol * np.max(np.abs(want))
+
+
+@pytest.mark.parametrize("N,nh,steps,prec,adj", [
+    (64, 4, 27, 0, False), (128, 4, 31, 0, False), (128, 4, 43, 0, True), (256, 4, 79, 0, False), (384, 4, 183, 0, False),
+    (512, 4, 145, 0, False), (64, 4, 31, 1, False), (256, 4, 75, 1, True), (384, 4, 319, 1, False), (384, 4, 200, 1, True)])
+def test_below_the_line_it_steps(tsk, N, nh, steps, prec, adj):
+    op, _ = _op(tsk, N, nh, steps, prec)
+    x, y, z = op.new_state(), op.new_state(), op.new_state()
+    x.copy_(torch.from_numpy(W.normal_real((x.numel(),), 4)))
+    apply = tsk.apply_adjoint if adj else tsk.apply
+    apply(op, x, y)
+    _step_only(tsk, op, True)
+    apply(op, x, z)
+    assert torch.equal(y, z)
 
 
 @pytest.mark.parametrize("prec", [0, 1])
