@@ -29,10 +29,10 @@
 // operands of all its workgroups).  The vector updates of the same doubling
 // read the same D, so they ride along as extra workgroups, one wavefront per row.
 // Bound: the matrix cores (4 x 64 cycles per FP64 tile and 4 k), for few small
-// matrices the launch and the load latency at its start.  One doubling, FP64: one
-// matrix of 256 14.5 us, of 400 21.6, of 1000 137; 42 of 85 (dense) 13.8, 63 of 127
-// 31 with the vector rows, 85 of 171 106 (32 TFLOP/s).  The rows launched between
-// the tiles instead of after them: 42 against 31.
+// matrices the launch and the load latency at its start.  One doubling, FP64, as traced: one
+// matrix of 256 16.5 us, of 400 23.7, of 1000 138; 42 of 85 (dense) 14.5, 63 of 127 26
+// with the vector rows, 85 of 171 90 (38 TFLOP/s).  The rows launched between the tiles
+// instead of after them: 42 against 31 for the 63.
 #pragma once
 
 #include <algorithm>

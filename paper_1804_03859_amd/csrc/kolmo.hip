@@ -569,13 +569,16 @@ inline bool power_pays(int M, int nh, int nsteps, bool fp32, bool adj) {
 }
 
 // Squaring (colmatrix.hpp) or the column stepper, for a profile of harmonics up to h.
-// Measured, 3 harmonics, FP64, us (stepping / squaring): 10, 20, 60 and 200 steps of
-// 32^2 38/32 74/37 214/43 704/51; 96^2 51/44 98/51 287/63 947/77; 128^2 30/73 56/88 160/108
-// 526/135; 192^2 54/132 104/162 301/204 997/257; 256^2 57/255 109/311 318/469 1052/617;
-// 384^2 133/427 258/564 759/842 2522/1356; 512^2 114/868 229/1090 661/1602 2190/3453.  FP32
-// squares at 0.5 to 0.8 of that.  kStep64, kStep32: a step of the column stepper in us;
-// the estimate of squaring is within a third of the times above.  Fewer than 16 steps
-// always step: there is little to gain.
+// Measured, 3 harmonics, us (stepping / squaring), 20, 60 and 200 steps, FP64: 32^2 73/40
+// 213/48 700/58; 96^2 97/50 286/62 943/77; 128^2 56/- 159/101 525/124; 192^2 103/- 299/195
+// 994/238; 256^2 109/- 318/- 1049/589; 384^2 257/- 759/- 2510/1282; FP32: 32^2 67/31 194/35
+// 634/42; 128^2 44/- 123/66 404/83; 256^2 88/- 255/- 838/380; 384^2 191/- 557/549 1849/802.
+// At the lines: FP64 128^2 33 steps 89/86, 192^2 39 steps 196/184, 256^2 106 steps 559/499,
+// 512^2 458 steps 4988/4951; FP32 384^2 57 steps 531/537, 512^2 362 steps 2697/2193 (with a
+// margin of 1.1 instead of 1.2: FP64 128^2 29 steps 79/86, 512^2 404 steps 4400/4621, FP32
+// 384^2 47 steps 438/483).  kStep64, kStep32: a step of the column stepper in us; the
+// estimate of squaring is within a third of the times above.  Fewer than 16 steps always
+// step: there is little to gain.
 struct ColumnPlan {
     bool square = false;
     int doublings = 0;
@@ -592,7 +595,7 @@ inline ColumnPlan column_plan(int N, int M, int h, int nsteps, bool fp32) {
     double cost = 0.0;
     p.doublings = c.doublings(nsteps, b4, &cost);
     cost += 6.0 + c.product(b1, b1) + 2.0 * c.product(b1, b4);
-    p.square = nsteps >= 16 && 1.1 * cost < (fp32 ? kStep32 : kStep64)[i] * nsteps;
+    p.square = nsteps >= 16 && 1.2 * cost < (fp32 ? kStep32 : kStep64)[i] * nsteps;
     return p;
 }
 
