@@ -827,13 +827,18 @@ def cn_pcr_flops(n, levels):
 
 def cn_square_flops(n, nsteps):
     """Flops of one integration by squaring as executed: a dense complex product of the
-    padded matrix (8 n^3) and two matrix-vector products per doubling, and the last
-    applications."""
-    dbl, app = max(4.0 + 0.05 * n, 8.0 * n ** 3 / 6.6e7), 3.3 + 0.001 * n  # the library's cost model, us
-    k = 0
-    while (nsteps >> k) - (nsteps >> (k + 1)) > dbl / app:
-        k += 1
-    ld = (n + 31) // 32 * 32
+    padded matrix (8 ld^3) and two matrix-vector products per doubling, and the last
+    applications; doublings and padding as the library chooses them (CpowCost, CpowWork)."""
+    w = 32 if ((n + 15) // 16) ** 2 >= 3072 else 16
+    ld = (n + w - 1) // w * w
+    doubling = 2.8 + 0.045 * min(ld, 256) + 8.0 * ld ** 3 / 6.0e7  # us
+    application = 2.8 + 16.0 * ld ** 2 / 7.0e6
+    best, k, spent = None, 0, 0.0
+    for i in range(nsteps.bit_length()):
+        total = spent + (nsteps >> i) * application
+        if best is None or total < best:
+            best, k = total, i
+        spent += doubling
     return k * (8 * ld ** 3 + 16 * ld ** 2) + (nsteps >> k) * 8 * ld ** 2
 
 
