@@ -79,8 +79,8 @@ def integrates_by_squaring(N, nsteps, fp32, nh=4):
     """Whether a plain forward matvec of a one-harmonic base flow squares the step matrix of
     its chains (the library's rule: step counts by tiles of 16 modes)."""
     t = power_tiles(N, nh)
-    least = ((24, 32, 64, None, 80, 80) if fp32 else (16, 32, 76, 176, 140, 140))
-    return t <= 6 and 1 + (N - 1) // 3 * (nh // 2 + 1) <= 768 and least[t - 1] is not None and nsteps >= least[t - 1]
+    least = ((32, 32, 64, 320, 80, 80) if fp32 else (28, 32, 80, 184, 146, 146))
+    return t <= 6 and 1 + (N - 1) // 3 * (nh // 2 + 1) <= 768 and nsteps >= least[t - 1]
 
 
 def power_flops(N, nsteps, nh=4):
@@ -201,7 +201,8 @@ def run_sweep(args, tsk, W, np, torch):
     # cycles run as captured graphs, not timed per matvec).  Flops: each instance's
     # own matvecs of that phase (at most m = 64).
     ms_apply = rb[0]["ms_apply"]
-    # every instance of this base runs the spectral-coupling stepper, all grid sizes in one launch
+    # every instance of this base is split into chains: one launch squares those of 128^2 and 256^2, one steps those
+    # of 384^2
     flops_total = sum(min(b["n_matvec"], 64) * stepper_flops(tsk, op, c["N"], nsteps)[0]
                       for b, c, op in zip(rb, sweep, ops))
     achieved = flops_total / (ms_apply / 1e3) / 1e12
@@ -216,7 +217,8 @@ def run_sweep(args, tsk, W, np, torch):
                    "n_matvec": [b["n_matvec"] for b in rb], "status": [b["status"] for b in rb],
                    "restarts": [b["n_restarts"] for b in rb],
                    "batched_matvec_ms_total": ms_apply},
-        "roofline": {"bound": "alu", "kernel": "k_colstep_couple<float,1> (one batched matvec of all active instances)",
+        "roofline": {"bound": "alu", "kernel": "k_couple_power_batch<float> and k_colstep_couple<float,1> (one batched matvec of "
+                                               "all active instances)",
                      "achieved": achieved, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP32_VECTOR_PEAK_TFLOPS, "matvec_ms_total": ms_apply,
                      "flops_total": flops_total, "traffic": None},

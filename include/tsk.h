@@ -129,15 +129,18 @@ tsk_status tsk_set_base_flow(tsk_op op, const double* U, const double* V,
  * 2/3 rule nothing of the pseudo-spectral product wraps onto a kept mode
  * (n < N - 2M), so it is the same operator to rounding.  A chain is advanced
  * step by step by one wavefront or, where that is faster, by repeated squaring of
- * its one-step matrix within the call (nothing is kept between calls).  Other
- * profiles: tsk_apply and tsk_apply_adjoint of many steps square the one-step
- * matrices of whole columns where that is faster (in memory for four matrices per
- * column, allocated on first use and shared by the operators of one stream; captured
- * calls, calls on hipStreamPerThread and calls that find no memory step); otherwise, and in tsk_arnoldi and the batch drivers, the column stepper, whose kx
- * columns per 64-lane wavefront (1 or 2, 2 only for N <= 256) the library times on
- * the first matvec of a given size, precision, base kind and launch size that steps
- * and keeps for the process.  1 or 2 force that column variant (both compute every column with
- * the same arithmetic, so results do not depend on the choice); 3 forces the
+ * its one-step matrix within the call (nothing is kept between calls; a mode that
+ * the integration damps keeps its own accuracy, as in stepping).  Other profiles:
+ * tsk_apply, tsk_apply_adjoint and tsk_krylov_schur of many steps square the
+ * one-step matrices of whole columns where that is faster (in memory for four
+ * matrices per column, allocated on first use and shared by the operators of one
+ * stream; captured calls, calls on hipStreamPerThread and calls that find no memory
+ * step); otherwise, and in tsk_arnoldi and the batch drivers, the column stepper,
+ * whose kx columns per 64-lane wavefront (1 or 2, 2 only for N <= 256) the library
+ * times on the first matvec of a given size, precision, base kind and launch size
+ * that steps and keeps for the process.  1 or 2 force that column variant (both
+ * compute every column with the same arithmetic, so results do not depend on the
+ * choice); 3 forces the
  * Bloch-sector stepper where it applies (N = 128, 256 or 512 and a profile of
  * period 2 pi / 4 with a single harmonic: each column split into the four
  * sectors ky = 4m + r, exact N/4-point products), else the column stepper.
@@ -148,9 +151,9 @@ tsk_status tsk_set_tuning(tsk_op op, int columns_per_wave);
 tsk_status tsk_get_tuning(tsk_op op, int* columns_per_wave);
 
 /* Launch shape of the spectral-coupling stepper (of chains advanced step by step;
- * integrations by squaring have a shape of their own and report 4): 64-lane
- * wavefronts per workgroup (1, 2 or 4; one chain per wavefront in every shape, so the results
- * are the same bits).  0 (the default) lets the library time the three shapes
+ * integrations by squaring have a shape of their own, report 4 and stay so with a
+ * forced shape): 64-lane wavefronts per workgroup (1, 2 or 4; one chain per
+ * wavefront in every shape, so the results are the same bits).  0 (the default) lets the library time the three shapes
  * on the first launch of a given precision, chain layout and launch size (a
  * single matvec, or a batch's shared launch) and keep the fastest for the
  * process.  tsk_get_stepper_waves reports the forced shape, else the shape of
@@ -246,7 +249,8 @@ tsk_status tsk_optimal_perturbation(tsk_op op, int m, int k, double tol, const v
  * operators of one state type and one stream, each with an adjoint, advance
  * their Lanczos iterations in lockstep; the integrations of Ginzburg-Landau
  * instances of one node count (the resolvent of each at its own frequency, or
- * its propagator) run in one launch per pass, one workgroup per instance.  Each
+ * its propagator) run in one launch per pass, one workgroup per instance, or are
+ * squared together.  Each
  * instance stops on its own test.  Arguments as for tsk_optimal_perturbation,
  * per instance i: v0_devs[i] (array or entries may be NULL), seeds[i] (NULL
  * array: seed i), sigma + k i, resid + k i, vecs_devs[i] (array or entries may
