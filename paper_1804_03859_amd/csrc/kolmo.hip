@@ -782,6 +782,7 @@ struct KolmoOp final : Operator {
         if (hmax < 0) {  // the parameters came after the profile
             hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
             if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+            Scratch::Relaxed relaxed;
             std::vector<double> h(4 * size_t(N));
             profile_dft(h.data());
             if (hipMemcpyAsync(prof.ptr, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, stream) !=

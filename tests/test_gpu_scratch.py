@@ -80,3 +80,41 @@ def test_threads_with_operators_on_one_stream(tsk):
     for t in ts:
         t.join()
     assert not errors
+
+
+@pytest.mark.parametrize("late", [False, True])
+def test_first_squared_call_while_another_stream_captures(tsk, late):
+    # the memory, and the transform of a profile that was set before the parameters (late), come legally
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(s1):
+        cop = tsk.create_kolmo2d(64, 0)
+        tsk.set_params_kolmo(cop, 20.0, 0.5, 0.005, 1.0)
+        tsk.set_base_kolmogorov(cop, 4)
+        cx, cy, cz = cop.new_state(), cop.new_state(), cop.new_state()
+        cx.copy_(torch.from_numpy(W.normal_real((cx.numel(),), 1)))
+        tsk.apply(cop, cx, cy)
+    with torch.cuda.stream(s2):
+        ref = _shear(tsk, 96)
+        y = 2 * np.pi * np.arange(96) / 96
+        op = tsk.create_kolmo2d(96, 0)
+        if not late:
+            tsk.set_params_kolmo(op, 20.0, 0.5, 0.005, 1.0)
+        tsk.set_base_parallel(op, 0.7 * np.sin(y) + 0.3 * np.sin(2 * y + 0.6), 0.7 * np.sin(y) + 1.2 * np.sin(2 * y + 0.6))
+        if late:
+            tsk.set_params_kolmo(op, 20.0, 0.5, 0.005, 1.0)
+        out = op.new_state()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s1):
+        tsk.apply(cop, cx, cz)
+        tsk.apply(op, ref[1], out)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        cz.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(cy, cz)
+    tsk.apply(*ref)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref[2])
